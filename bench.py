@@ -647,8 +647,12 @@ def main():
     if args.shared_vars:
         kname = f"lpa::k_move_sv<{kk}, {wide}>"
     else:
+        # the single-scan kernel has an instance for det launches with hubs
+        hubs = (args.mode == "det"
+                and int((rp[1:] - rp[:-1]).max()) > (args.lane_max_degree or 4096))
         kname = (f"lpa::k_move{'_rescan' if args.rescan else ''}"
-                 f"<{kk}, {'true' if args.mode == 'async' else 'false'}, {wide}>")
+                 f"<{kk}, {'true' if args.mode == 'async' else 'false'}, {wide}"
+                 f"{'' if args.rescan else ', true' if hubs else ', false'}>")
     traffic = traffic_from_profiles(kname,
                                     workload, digest)
     result = {

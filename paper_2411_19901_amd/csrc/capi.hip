@@ -415,13 +415,14 @@ struct lpa_batch {
   hipStream_t cap_stream = nullptr;  // private stream the iterations are captured on
   hipGraph_t graph = nullptr;
   hipGraphExec_t graph_exec = nullptr;
-  long long graph_key[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+  std::array<long long, 10> graph_key{};
   bool async_mode = false;
   hipStream_t stream = nullptr;
   int device = 0;
   int check_every = 0;
   int cus = 1;
-  int grid_cap[2] = {1, 1};  // resident k_move workgroups: int32 / int64 positions
+  // resident k_move workgroups: [int32 / int64 positions][without / with det hubs]
+  int grid_cap[2][2] = {{1, 1}, {1, 1}};
   int blocks_cap = 0;        // lpa_config.move_blocks_per_cu (0: as many as fit)
   bool wide = false;         // a loaded graph has int64 row offsets
   void *dblock = nullptr;  // device: descriptors, prefixes, finished counter, status
@@ -438,6 +439,7 @@ struct lpa_batch {
   size_t off_prefix = 0, off_finished = 0, off_status = 0;
   std::vector<lpa_handle *> loaded;
   int total_items = 0, total_hubs = 0, total_merge = 0, total_segs = 0, unfinished = 0;
+  int det_hubs = 0;  // det mode: hubs of the loaded unfinished graphs
   bool poisoned = false;
   std::string err;
 };
@@ -808,11 +810,13 @@ int batch_alloc(lpa_batch *b) {
   b->device = dev;
   if (hipDeviceGetAttribute(&b->cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return LPA_ERR_HIP;
-  for (int wide = 0; wide < 2; ++wide) {
-    int per_cu = move_blocks_per_cu(b->k, b->async_mode, b->rescan, b->shared_vars, wide != 0);
-    if (b->blocks_cap > 0 && b->blocks_cap < per_cu) per_cu = b->blocks_cap;
-    b->grid_cap[wide] = b->cus * per_cu;
-  }
+  for (int wide = 0; wide < 2; ++wide)
+    for (int hubs = 0; hubs < 2; ++hubs) {
+      int per_cu = move_blocks_per_cu(b->k, b->async_mode, b->rescan, b->shared_vars, wide != 0,
+                                      hubs != 0);
+      if (b->blocks_cap > 0 && b->blocks_cap < per_cu) per_cu = b->blocks_cap;
+      b->grid_cap[wide][hubs] = b->cus * per_cu;
+    }
   if (b->capture && hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking) != hipSuccess) {
     (void)hipGetLastError();
     return LPA_ERR_HIP;
@@ -840,6 +844,7 @@ int batch_load(lpa_batch *b, lpa_handle *const *hs, int count) {
           *pm = b->h_prefix + 2 * (b->capacity + 1), *ps = b->h_prefix + 3 * (b->capacity + 1);
   pi[0] = ph[0] = pm[0] = ps[0] = 0;
   int unfinished = 0;
+  int64_t det_hubs = 0;
   bool wide = false;
   for (int g = 0; g < count; ++g) {
     lpa_handle *h = hs[g];
@@ -857,6 +862,7 @@ int batch_load(lpa_batch *b, lpa_handle *const *hs, int count) {
     b->h_desc[g] = h->desc;
     const bool live = !h->finished;
     unfinished += live ? 1 : 0;
+    det_hubs += live && !b->async_mode ? h->desc.n_hubs : 0;
     const int64_t next[4] = {
         (int64_t)pi[g] + (live ? move_items(h) : 0),
         (int64_t)ph[g] + (live && b->async_mode ? h->desc.n_hubs : 0),
@@ -875,6 +881,7 @@ int batch_load(lpa_batch *b, lpa_handle *const *hs, int count) {
   b->total_merge = pm[count];
   b->total_segs = ps[count];
   b->unfinished = unfinished;
+  b->det_hubs = (int)det_hubs;  // each is a work item: no more than total_items
   b->wide = wide;
   b->loaded.assign(hs, hs + count);
   HIP_TRY_B(b, hipMemcpyAsync(b->d_desc, b->h_desc, (size_t)count * sizeof(GraphDesc),
@@ -897,6 +904,7 @@ Launch make_launch(lpa_batch *b) {
   L.total_hubs = b->total_hubs;
   L.total_merge = b->total_merge;
   L.total_segs = b->total_segs;
+  L.det_hubs = b->det_hubs;
   L.finished = b->d_finished;
   L.status_out = b->d_status;
   L.no_finish = 0;
@@ -928,7 +936,8 @@ int batch_iterate(lpa_batch *b, int iters, lpa_handle *prof) {
   const Launch L = make_launch(b);
   const int waves_per_block = kBlock / kWave;
   int grid = (b->total_items + waves_per_block - 1) / waves_per_block;
-  if (grid > b->grid_cap[b->wide]) grid = b->grid_cap[b->wide];
+  const int cap = b->grid_cap[b->wide][L.det_hubs > 0];
+  if (grid > cap) grid = cap;
   if (grid < 1) grid = 1;
   int mg = (b->total_merge + waves_per_block - 1) / waves_per_block;
   if (mg > b->cus * 4) mg = b->cus * 4;
@@ -938,9 +947,10 @@ int batch_iterate(lpa_batch *b, int iters, lpa_handle *prof) {
     // every remaining iteration as one hipGraph, captured on a private
     // stream once per launch shape and replayed on the caller's stream
     // (the descriptor table it reads is uploaded before each replay)
-    const long long key[9] = {iters, grid, mg, L.G, L.total_items, L.total_hubs, L.total_merge,
-                              L.total_segs, b->wide};
-    if (!b->graph_exec || memcmp(key, b->graph_key, sizeof(key)) != 0) {
+    const std::array<long long, 10> key = {iters,        grid,          mg,           L.G,
+                                           L.total_items, L.total_hubs, L.total_merge,
+                                           L.total_segs,  b->wide,      L.det_hubs > 0};
+    if (!b->graph_exec || key != b->graph_key) {
       if (b->graph_exec) (void)hipGraphExecDestroy(b->graph_exec);
       if (b->graph) (void)hipGraphDestroy(b->graph);
       b->graph_exec = nullptr;
@@ -960,7 +970,7 @@ int batch_iterate(lpa_batch *b, int iters, lpa_handle *prof) {
       HIP_TRY_B(b, ee);
       b->graph = g;
       HIP_TRY_B(b, hipGraphInstantiate(&b->graph_exec, g, nullptr, nullptr, 0));
-      memcpy(b->graph_key, key, sizeof(key));
+      b->graph_key = key;
     }
     HIP_TRY_B(b, hipGraphLaunch(b->graph_exec, b->stream));
     return LPA_OK;
@@ -1301,7 +1311,7 @@ int stream_bin(lpa_handle *h) {
   S.grid_cap = cus * move_blocks_per_cu(kernel_k(h->k, h->flags), h->async_mode,
                                         (h->flags & LPA_RESCAN) != 0,
                                         (h->flags & LPA_SHARED_VARS) != 0,
-                                        h->row_ptr.p64 != nullptr);
+                                        h->row_ptr.p64 != nullptr, true);
   return LPA_OK;
 }
 
@@ -1377,6 +1387,7 @@ int stream_iterate(lpa_handle *h, int iters) {
       Lp.total_hubs = h->async_mode ? S.hubs[p] : 0;
       Lp.total_merge = h->async_mode ? (S.hubs[p] + kMergeHubs - 1) / kMergeHubs : 0;
       Lp.total_segs = S.segs[p];
+      Lp.det_hubs = h->async_mode ? 0 : S.hubs[p];
       Lp.no_finish = 1;
       int grid = (S.items[p] + waves_per_block - 1) / waves_per_block;
       grid = std::max(1, std::min(grid, S.grid_cap));

@@ -158,6 +158,7 @@ struct Launch {
   int32_t total_hubs;
   int32_t total_merge;
   int32_t total_segs;
+  int32_t det_hubs;         // det mode: hubs of all its graphs, one wavefront each (0: none)
   int32_t *finished;        // graphs that have finished (counter)
   int32_t *status_out;      // [3 * G]: iter, done, dN of the iteration just run (0: none)
   int32_t no_finish;        // 1: launch_iteration leaves out the stop test (k_finish)
@@ -207,7 +208,9 @@ struct MoveArgs {
 hipError_t launch_iteration(int k, bool async_mode, bool rescan, bool hub_shared,
                             bool shared_vars, bool wide, const Launch &L, int grid,
                             int merge_grid, hipStream_t s, hipEvent_t ev_beg, hipEvent_t ev_end);
-int move_blocks_per_cu(int k, bool async_mode, bool rescan, bool shared_vars, bool wide);
+// Resident workgroups of the move kernel per compute unit; hubs: of the kernel
+// for launches with det_hubs > 0.
+int move_blocks_per_cu(int k, bool async_mode, bool rescan, bool shared_vars, bool wide, bool hubs);
 // The stop test alone (k_finish): an iteration split over id ranges of a
 // graph runs launch_iteration once per range with Launch::no_finish set,
 // then this once.

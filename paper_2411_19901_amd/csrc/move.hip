@@ -330,12 +330,13 @@ constexpr int kMarkUnroll = 4;
 
 template <int U = kMarkUnroll, class Pos>
 __device__ __forceinline__ void mark_row(const MoveArgs &a, Pos beg, Pos end, int lane) {
-  for (Pos q0 = beg; q0 < end; q0 += U * kWave) {
+  const unsigned len = (unsigned)(end - beg);  // a row has fewer than 2^31 entries
+  for (unsigned q0 = 0; q0 < len; q0 += U * kWave) {
     int c[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const Pos q = q0 + u * kWave + lane;
-      c[u] = q < end ? __builtin_nontemporal_load(a.col + q) : -1;
+      const unsigned q = q0 + u * kWave + lane;
+      c[u] = q < len ? __builtin_nontemporal_load(a.col + (beg + (Pos)q)) : -1;
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
@@ -468,40 +469,510 @@ __device__ __forceinline__ void hub_feed(const MoveArgs &a, int self, Pos beg, P
   __builtin_amdgcn_s_setprio(0);
 }
 
-// Smallest value of lanes 0..K-1 for K = 16 or 32, in every lane: rotations
-// within each 16-lane row, then the two rows' minima for K = 32.  A minimum
-// is exact, so the order of the reduction does not matter.  (For k <= 8 the
-// K independent lane reads are the shorter chain.)
-template <int K>
-__device__ __forceinline__ float slot_min(float val, int lane) {
-  static_assert(K == 16 || K == 32, "slot_min: 16 or 32 slots");
-  float t = lane < K ? val : __int_as_float(0x7f800000);
-  t = fminf(t, dpp_f<0x128>(t));  // row_ror:8
-  t = fminf(t, dpp_f<0x124>(t));  // row_ror:4
-  t = fminf(t, dpp_f<0x122>(t));  // row_ror:2
-  t = fminf(t, dpp_f<0x121>(t));  // row_ror:1
-  float m = rl_f(t, 0);
-  if constexpr (K > 16) m = fminf(m, rl_f(t, 16));
-  return m;
+// The det hub chains: one wavefront feeds one row, entry by entry, into a
+// sketch held one slot per lane.  The chain is serial, so its time is the
+// instructions issued per entry.  One wavefront issues a dependent vector
+// instruction every 4.4 cycles, but a value that passes from a vector compare
+// through a scalar register to a branch or back to the vector unit costs 28
+// to 36 (measured), so the common step is straight vector code, and what would
+// need a branch is looked for in groups of kHubGroup entries.
+//
+// The row is read kHubChunk entries at a time, two chunks ahead (HubReader):
+// a chunk's columns are in flight while the chunk before it waits for its
+// labels, which arrive while the one before that is consumed.  A chunk's
+// entries that count (not the vertex itself) are appended to a queue in LDS,
+// from which every lane reads the same entry, so there is no cross-lane read
+// and no wait for memory inside the chain; the chain takes the queue kWave
+// entries at a time.
+constexpr int kHubChunk = 256;
+constexpr int kHubGroup = 8;
+constexpr int kHubParts = kHubChunk / kWave;
+constexpr int kHubQueue = kHubChunk + kWave;  // a chunk and what the chain has not taken yet
+constexpr int kNoLabel = -2;  // no vertex's label
+
+// The queue in kHubWords words of this wavefront's LDS, 16-byte aligned: labels
+// (2 * kHubGroup words of no label lie before the first) and weights.
+constexpr int kHubWords = 2 * kHubGroup + 2 * kHubQueue;
+static_assert(kHubWords <= kWave * (kStageT + 1), "the queue lies in the row stage");
+struct HubQueue {
+  int *lab;
+  float *wt;
+  __device__ __forceinline__ HubQueue(int *buf, int lane)
+      : lab(buf + 2 * kHubGroup), wt(reinterpret_cast<float *>(buf + 2 * kHubGroup + kHubQueue)) {
+    if (lane < 2 * kHubGroup) buf[lane] = kNoLabel;
+  }
+};
+
+// Offsets are from the row's first entry: a row has fewer than 2^31 entries, so
+// they and the chunks beyond its end fit 32 bits whatever the width of Pos.
+// Lanes past the end read the last entry again: without a branch around the
+// loads no register is copied, and none is waited for before it is used.
+template <bool UNIT, class Pos>
+struct HubReader {
+  int col[kHubParts], lab[kHubParts];
+  float x[kHubParts];
+  unsigned skip;  // bit d: part d's entry of this lane counts for nothing
+
+  __device__ __forceinline__ void cols(const MoveArgs &a, Pos beg, unsigned len, int lane,
+                                       unsigned o) {
+#pragma unroll
+    for (int d = 0; d < kHubParts; ++d) {
+      const unsigned e = min(o + d * kWave + lane, len - 1);
+      col[d] = __builtin_nontemporal_load(a.col + (beg + (Pos)e));
+    }
+  }
+  // of the columns held in col, at o
+  __device__ __forceinline__ void labels(const MoveArgs &a, int self, Pos beg, unsigned len,
+                                         int lane, unsigned o) {
+    skip = 0;
+#pragma unroll
+    for (int d = 0; d < kHubParts; ++d) {
+      lab[d] = a.C[col[d]];
+      skip |= (o + d * kWave + lane >= len || col[d] == self) ? 1u << d : 0u;
+    }
+    if constexpr (!UNIT) {
+      if (a.w) {
+#pragma unroll
+        for (int d = 0; d < kHubParts; ++d) {
+          const unsigned e = min(o + d * kWave + lane, len - 1);
+          x[d] = __builtin_nontemporal_load(a.w + (beg + (Pos)e));
+        }
+      }
+    }
+  }
+};
+
+// Queues the entries of [beg, end) that count and for which drop(lab, on) does
+// not hold (it is called by all lanes, on: the lane's entry counts), and calls
+// block(q) for queue entries q .. q + 63 as they fill up; returns the number
+// of entries then left in the queue, fewer than 64, from its start.
+template <bool UNIT, class Pos, class Drop, class Block>
+__device__ __forceinline__ int hub_rows(const MoveArgs &a, const HubQueue &Q, int self, Pos beg,
+                                        Pos end, int lane, Drop &&drop, Block &&block) {
+  const unsigned len = (unsigned)(end - beg);
+  if (len == 0) return 0;
+  // The chain of one hub bounds the whole iteration while the other
+  // wavefronts of its SIMD stream short rows: let it issue first.
+  __builtin_amdgcn_s_setprio(3);
+  HubReader<UNIT, Pos> R;
+#pragma unroll
+  for (int d = 0; d < kHubParts; ++d) R.x[d] = 1.0f;
+  R.cols(a, beg, len, lane, 0);
+  R.labels(a, self, beg, len, lane, 0);
+  R.cols(a, beg, len, lane, kHubChunk);
+  int n = 0;
+  for (unsigned o = 0; o < len; o += kHubChunk) {
+    const unsigned long long below = (1ull << lane) - 1ull;
+    drop.chunk();
+#pragma unroll
+    for (int d = 0; d < kHubParts; ++d) {
+      const bool counts = !((R.skip >> d) & 1u);
+      const bool dropped = drop(R.lab[d], counts);
+      const bool on = counts && !dropped;
+      const unsigned long long m = __ballot(on);
+      const int at = n + (int)__popcll(m & below);
+      if (on) {
+        Q.lab[at] = R.lab[d];
+        if constexpr (!UNIT) Q.wt[at] = R.x[d];
+      }
+      n += (int)__popcll(m);
+    }
+    wave_lds_sync();
+    R.labels(a, self, beg, len, lane, o + kHubChunk);
+    R.cols(a, beg, len, lane, o + 2 * kHubChunk);
+    int q = 0;
+    for (; q + kWave <= n; q += kWave) block(q);
+    if (q > 0) {  // what is left moves to the front
+      const int l = Q.lab[q + lane];
+      float w = 1.0f;
+      if constexpr (!UNIT) w = Q.wt[q + lane];
+      wave_lds_sync();
+      Q.lab[lane] = l;
+      if constexpr (!UNIT) Q.wt[lane] = w;
+      wave_lds_sync();
+      n -= q;
+    }
+  }
+  __builtin_amdgcn_s_setprio(0);
+  return n;
 }
 
-// Adds the entries `run` (lanes whose label is a key, slot: that key's slot)
-// to their slots.  UNIT: every such entry weighs 1 and every slot value is
-// an integer below 2^24 (unit weights on a row shorter than 2^24 entries),
-// so each slot takes its count of entries at once, exactly the sum that
-// adding them one by one in CSR order gives; otherwise one entry at a time
-// in lane order, with scalar lane indices and no cross-lane votes.
-template <bool UNIT>
-__device__ __forceinline__ void add_hits(unsigned long long run, int slot, float x, int lane,
-                                         float &val) {
-  if constexpr (UNIT) {
-    while (run) {
-      const int s = rl(slot, __ffsll((long long)run) - 1);
-      const unsigned long long ms = __ballot(slot == s) & run;
-      run &= ~ms;
-      val = (lane == s) ? val + (float)(int)__popcll(ms) : val;
+struct DropNone {
+  __device__ __forceinline__ void chunk() {}
+  __device__ __forceinline__ bool operator()(int, bool) { return false; }
+};
+
+// Keeps the reads of the next group's entries where they are written: before
+// this group is consumed.
+__device__ __forceinline__ void reads_start_here() { asm volatile("" ::: "memory"); }
+
+// Calls step(label, weight) for queue entries [q, q + 64) in order, all lanes
+// with the same entry.
+template <class Step>
+__device__ __forceinline__ void hub_each(const HubQueue &Q, int q, Step &&step) {
+  const int4 *l4 = reinterpret_cast<const int4 *>(Q.lab + q);
+  const float4 *w4 = reinterpret_cast<const float4 *>(Q.wt + q);
+  int4 nl = l4[0];
+  float4 nw = w4[0];
+#pragma unroll 2
+  for (int i = 0; i < kWave / 4; ++i) {
+    const int4 l = nl;
+    const float4 w = nw;
+    const int ni = (i + 1) & (kWave / 4 - 1);
+    nl = l4[ni];
+    nw = w4[ni];
+    reads_start_here();
+    step(l.x, w.x);
+    step(l.y, w.y);
+    step(l.z, w.z);
+    step(l.w, w.w);
+  }
+}
+
+// Calls step(label, weight) for every entry of [beg, end) that counts, in CSR
+// order, all lanes with the same entry.
+template <class Pos, class Step>
+__device__ __forceinline__ void hub_stream(const MoveArgs &a, int *buf, int self, Pos beg, Pos end,
+                                           int lane, Step &&step) {
+  const HubQueue Q(buf, lane);
+  const int n = hub_rows<false>(a, Q, self, beg, end, lane, DropNone(),
+                                [&](int q) { hub_each(Q, q, step); });
+#pragma unroll 1
+  for (int q = 0; q < n; ++q) step(Q.lab[q], Q.wt[q]);
+  wave_lds_sync();
+}
+
+// Slots across lanes: for K <= 16 each 16-lane row holds a copy of the sketch
+// (its lanes 0 .. K - 1; a group's entries are looked up one per row), for
+// K = 32 lanes 0 .. 31 do.  Slots are kept in increasing order of value, free
+// slots first (the slots' positions do not change the choice); the other lanes
+// hold a value above every slot's.
+template <int K>
+constexpr unsigned kSlotMask = K >= 32 ? ~0u : (1u << (K & 31)) - 1u;
+
+template <int K>
+__device__ __forceinline__ int slot_of(int lane) {
+  return K <= 16 ? lane & 15 : lane;
+}
+
+// The value of slot 0.
+template <int K>
+__device__ __forceinline__ unsigned first_slot(unsigned v) {
+  if constexpr (K <= 16)
+    return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x150, 0xF, 0xF, true);  // row_newbcast
+  else
+    return (unsigned)rfl((int)v);
+}
+
+// The value of the next slot; TOP above the last slot.
+template <int K, unsigned TOP>
+__device__ __forceinline__ unsigned next_slot(unsigned v) {
+  if constexpr (K == 16)  // no spare lane: a row shift whose last lane keeps TOP
+    return (unsigned)__builtin_amdgcn_update_dpp((int)TOP, (int)v, 0x101, 0xF, 0xF, false);
+  else
+    return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x134, 0xF, 0xF, true);  // wave_rol:1
+}
+
+// A slot's value grew to x: it moves up to its place.  p: the slot; c: its key.
+template <int K, unsigned TOP>
+__device__ __forceinline__ void slot_grew(int lane, int p, int c, unsigned x, int &key,
+                                          unsigned &v) {
+  const unsigned up = next_slot<K, TOP>(v);
+  const int kup = (int)next_slot<K, 0>((unsigned)key);
+  const unsigned nv = max(v, min(up, x));
+  const int nk = x > up ? kup : (x > v ? c : key);
+  const bool from = slot_of<K>(lane) >= p;
+  v = from ? nv : v;
+  key = from ? nk : key;
+}
+
+// Runs queue entries [q, q + 64) in groups of kHubGroup.  fast(c, w) is the
+// step of an entry whose label is in no slot, slow(c, w) looks the label up
+// first; an entry takes the fast step when its label is in no slot and repeats
+// none of the 15 entries before it, and most groups hold no other.  A group's
+// labels are looked up (two compares: row r of the lanes takes entries r and
+// r + 4) before the group ahead of it runs, so that nothing waits for the
+// answer; the keys which that group adds are among those 15 labels.
+// key: the slots' keys, K <= 16.
+template <int K, bool UNIT, class Fast, class Slow>
+__device__ __forceinline__ void hub_groups(const HubQueue &Q, int q, int lane, const int &key,
+                                           Fast &&fast, Slow &&slow) {
+  static_assert(kHubGroup == 8, "two lookups of four entries");
+  struct Group {
+    int4 l[2];
+    float4 w[2];
+  };
+  auto fetch = [&](Group &g, int i) {
+    const int4 *l4 = reinterpret_cast<const int4 *>(Q.lab + i);
+    g.l[0] = l4[0];
+    g.l[1] = l4[1];
+    if constexpr (!UNIT) {
+      const float4 *w4 = reinterpret_cast<const float4 *>(Q.wt + i);
+      g.w[0] = w4[0];
+      g.w[1] = w4[1];
     }
+  };
+  const int *look = Q.lab + q + (lane >> 4);
+  unsigned long long rep;
+  {
+    const int *mine = Q.lab + q + lane;
+    const int e = mine[0];
+    unsigned least = ~0u;
+#pragma unroll
+    for (int t = 1; t < 2 * kHubGroup; ++t) least = min(least, (unsigned)(mine[-t] ^ e));
+    rep = __ballot(least == 0u);
+  }
+  Group A, B;
+  fetch(A, q);
+  unsigned long long h0 = __ballot(key == look[0]), h1 = __ballot(key == look[4]);
+  int la = look[8], lb = look[12];
+  auto run = [&](const Group &g, Group &nxt, int i) {  // i: offset of g in the 64 entries
+    const unsigned long long hits[2] = {h0, h1};
+    const unsigned rp = (unsigned)rep;
+    h0 = __ballot(key == la);
+    h1 = __ballot(key == lb);
+    rep >>= kHubGroup;
+    const int far = (i + 2 * kHubGroup) & (kWave - 1);
+    fetch(nxt, q + ((i + kHubGroup) & (kWave - 1)));
+    la = look[far];
+    lb = look[far + 4];
+    reads_start_here();
+    const int c[8] = {g.l[0].x, g.l[0].y, g.l[0].z, g.l[0].w, g.l[1].x, g.l[1].y, g.l[1].z, g.l[1].w};
+    float w[8];
+    if constexpr (UNIT) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) w[j] = 1.0f;
+    } else {
+      const float u[8] = {g.w[0].x, g.w[0].y, g.w[0].z, g.w[0].w,
+                          g.w[1].x, g.w[1].y, g.w[1].z, g.w[1].w};
+#pragma unroll
+      for (int j = 0; j < 8; ++j) w[j] = u[j];
+    }
+    if (hits[0] | hits[1] | (rp & 0xFF)) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const unsigned in = (unsigned)(hits[j >> 2] >> (16 * (j & 3))) & kSlotMask<K>;
+        if (in | ((rp >> j) & 1u))
+          slow(c[j], w[j]);
+        else
+          fast(c[j], w[j]);
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) fast(c[j], w[j]);
+    }
+  };
+#pragma unroll 1
+  for (int i = 0; i < kWave; i += 2 * kHubGroup) {
+    run(A, B, i);
+    run(B, A, i + kHubGroup);
+  }
+}
+
+// The sketch with weights.  Values are handled as bit patterns where they are
+// compared (non-negative floats order like unsigned integers).  With v0 the
+// smallest value, a pair (c, w) that no key holds does the same to every state:
+// every slot loses m = min(v0, w), and x = |v0 - w| takes the place of the
+// lowest slot's value: w - v0 under the key c if w > v0 (with a free slot
+// v0 = 0, so nothing is lost and w is placed), else v0 - w under its own key.
+// Subtraction of one m keeps the order, so x only moves up to its place, one
+// minimum and one maximum with the next slot's value: eleven vector
+// instructions, no branch, no search for the smallest or for a free slot.
+// A pair of weight 0 changes nothing.
+template <int K>
+__device__ __forceinline__ void weighted_miss(int c, float w, int &key, unsigned &v) {
+  const unsigned v0 = first_slot<K>(v), wb = __float_as_uint(w);
+  const float m = __uint_as_float(min(v0, wb));
+  const unsigned x = __float_as_uint(__uint_as_float(max(v0, wb)) - m);
+  const unsigned d = __float_as_uint(__uint_as_float(v) - m);
+  const unsigned up = next_slot<K, 0x7f800000u>(d);
+  const int kup = (int)next_slot<K, 0>((unsigned)key);
+  v = max(d, min(up, x));
+  key = x > up ? kup : (x > d ? c : key);
+}
+
+template <int K>
+__device__ __forceinline__ void weighted_entry(int lane, int c, float w, int &key, unsigned &v) {
+  const unsigned hm = (unsigned)__ballot(key == c) & kSlotMask<K>;
+  if (hm) {
+    const int p = __ffs((int)hm) - 1;
+    const unsigned x = __float_as_uint(rl_f(__uint_as_float(v), p) + w);
+    slot_grew<K, 0x7f800000u>(lane, p, c, x, key, v);
   } else {
+    weighted_miss<K>(c, w, key, v);
+  }
+}
+
+// One row with weights.  FRESH: every label differs from every key
+// (MoveArgs::fresh_hubs).  Measured on a row of 163,428 entries, k = 8: 30 ns
+// per entry FRESH, 35 to 43 with 0 to 5% of hits (one vote and one decision per
+// entry took 95 and 140 to 200).  R-MAT-21, k = 4, whose largest row has some
+// 100,000: 22 to 4.1 ms per iteration.
+template <int K, bool FRESH, class Pos>
+__device__ __forceinline__ void det_weighted(const MoveArgs &a, int *buf, int x0, Pos beg, Pos end,
+                                             int lane, int &key, float &val) {
+  unsigned v = slot_of<K>(lane) < K ? 0u : 0x7f800000u;
+  if constexpr (FRESH) {
+    hub_stream(a, buf, x0, beg, end, lane,
+               [&](int c, float w) { weighted_miss<K>(c, w, key, v); });
+  } else if constexpr (K > 16) {
+    hub_stream(a, buf, x0, beg, end, lane,
+               [&](int c, float w) { weighted_entry<K>(lane, c, w, key, v); });
+  } else {
+    const HubQueue Q(buf, lane);
+    const auto entry = [&](int c, float w) { weighted_entry<K>(lane, c, w, key, v); };
+    const int n = hub_rows<false>(a, Q, x0, beg, end, lane, DropNone(), [&](int q) {
+      hub_groups<K, false>(
+          Q, q, lane, key, [&](int c, float w) { weighted_miss<K>(c, w, key, v); }, entry);
+    });
+#pragma unroll 1
+    for (int q = 0; q < n; ++q) entry(Q.lab[q], Q.wt[q]);
+    wave_lds_sync();
+  }
+  val = slot_of<K>(lane) < K ? __uint_as_float(v) : 0.0f;
+}
+
+// The sketch with unit weights on a row of fewer than 2^24 entries: slot
+// values are whole numbers, exact in fp32, and are counted as integers.  An
+// entry that no key holds takes 1 from every slot and is used up when all are
+// live; otherwise it takes the last free slot, whose next slot is live: seven
+// vector instructions, and the slots stay in order.
+constexpr unsigned kUnitTop = 1u << 30;
+
+// 1 in a register whose value the compiler does not know: it would otherwise
+// turn a minimum with 1 into a comparison with 0, whose result goes through
+// scalar registers.
+__device__ __forceinline__ unsigned opaque_one() {
+  unsigned one = 1u;
+  asm("" : "+v"(one));
+  return one;
+}
+
+// one: 1, from opaque_one.
+template <int K>
+__device__ __forceinline__ void unit_miss(unsigned one, int c, int &key, unsigned &v) {
+  const unsigned m = min(first_slot<K>(v), one), t = min(next_slot<K, kUnitTop>(v), one);
+  const unsigned here = __builtin_elementwise_sub_sat(t, v);  // 1: v is 0 and the next is not
+  v = v - m + here;
+  key = here ? c : key;
+}
+
+template <int K>
+__device__ __forceinline__ void unit_entry(unsigned one, int lane, int c, int &key, unsigned &v) {
+  const unsigned hm = (unsigned)__ballot(key == c) & kSlotMask<K>;
+  if (hm) {
+    const int p = __ffs((int)hm) - 1;
+    slot_grew<K, kUnitTop>(lane, p, c, (unsigned)rl((int)v, p) + 1u, key, v);
+  } else {
+    unit_miss<K>(one, c, key, v);
+  }
+}
+
+// Leaves out of the chain the entries of the top slot's label, and counts them:
+// while the top slot holds more than the entries ahead could take from it, it
+// stays live whatever they are, so entries of its label only add to it, in
+// any order (on R-MAT graphs one label soon holds a tenth, later nearly all of
+// a hub's row).  Each time all slots lose 1, the other slots and the entry
+// that is used up lose K together, out of what these slots hold and the entries
+// add: at most (kHubQueue + (K - 1) * the second value) / K times.
+template <int K>
+struct DropTop {
+  int lane;
+  const int &key;
+  unsigned &v;
+  int top;
+  bool safe;
+  __device__ __forceinline__ DropTop(int l, const int &k, unsigned &x) : lane(l), key(k), v(x) {}
+  __device__ __forceinline__ void chunk() {
+    const long long others = K > 1 ? (long long)(K - 1) * rl((int)v, K > 1 ? K - 2 : 0) : 0;
+    safe = (long long)(rl((int)v, K - 1) - 1) * K > kHubQueue + others;
+    top = rl(key, K - 1);
+  }
+  __device__ __forceinline__ bool operator()(int lab, bool on) {
+    const bool heavy = on && safe && lab == top;
+    const unsigned tops = (unsigned)__popcll(__ballot(heavy));  // of the whole wavefront
+    v += slot_of<K>(lane) == K - 1 ? tops : 0u;
+    return heavy;
+  }
+};
+
+// One row with unit weights: 27 to 35 ns per entry of the chain on a row of
+// 163,428, k = 8 (140 with one vote and one decision per entry); R-MAT-22, k = 8,
+// iterations 1 to 5: 23 to 5.5 ms.
+template <int K, class Pos>
+__device__ __forceinline__ void det_unit(const MoveArgs &a, int *buf, int x0, Pos beg, Pos end,
+                                         int lane, int &key, float &val) {
+  const HubQueue Q(buf, lane);
+  const unsigned one = opaque_one();
+  unsigned v = slot_of<K>(lane) < K ? 0u : kUnitTop;
+  const auto entry = [&](int c, float) { unit_entry<K>(one, lane, c, key, v); };
+  const int n = hub_rows<true>(a, Q, x0, beg, end, lane, DropTop<K>(lane, key, v), [&](int q) {
+    if constexpr (K <= 16)
+      hub_groups<K, true>(
+          Q, q, lane, key, [&](int c, float) { unit_miss<K>(one, c, key, v); }, entry);
+    else
+#pragma unroll 1
+      for (int i = 0; i < kWave; ++i) entry(Q.lab[q + i], 1.0f);
+  });
+#pragma unroll 1
+  for (int q = 0; q < n; ++q) entry(Q.lab[q], 1.0f);
+  wave_lds_sync();
+  val = slot_of<K>(lane) < K ? (float)v : 0.0f;
+}
+
+// Unit weights at iteration 0 from the initial labels, no neighbour twice
+// (MoveArgs::fresh_hubs): every entry is a label of its own, so K entries fill
+// the slots and the next empties them all again.  What is left after L
+// entries is the last L mod (K + 1) of them, one slot each with value 1; the
+// row is only counted (the vertex itself is no entry).
+template <int K, class Pos>
+__device__ __forceinline__ void det_unit_fresh(const MoveArgs &a, int x0, Pos beg, Pos end,
+                                               int lane, int &key, float &val) {
+  constexpr int U = 16;
+  int own = 0;  // entries that are the vertex itself (at most one)
+  const unsigned len = (unsigned)(end - beg);
+  for (unsigned q0 = 0; q0 < len; q0 += U * kWave) {
+    int c[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const unsigned q = q0 + u * kWave + lane;
+      c[u] = q < len ? __builtin_nontemporal_load(a.col + (beg + (Pos)q)) : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) own += c[u] == x0 ? 1 : 0;
+  }
+  const unsigned entries = len - (unsigned)__popcll(__ballot(own != 0));
+  const int left = (int)(entries % (K + 1));
+  // the last 64 entries hold the last K + 1 that count
+  const int c = (unsigned)lane < len ? a.col[end - 1 - lane] : x0;
+  const bool counts = c != x0;
+  const int rank = (int)__popcll(__ballot(counts) & ((1ull << lane) - 1ull));
+  const bool live = counts && rank < left;
+  // lane s takes the rank-s entry
+  const unsigned long long lm = __ballot(live);
+  const int l = live ? a.C[c] : -1;
+  unsigned long long rest = lm;
+#pragma unroll
+  for (int s = 0; s < K; ++s) {
+    const bool on = rest != 0;
+    const int ls = rl(l, on ? __ffsll((long long)rest) - 1 : 0);
+    rest &= rest - 1;
+    key = on && lane == s ? ls : key;
+    val = on && lane == s ? 1.0f : val;
+  }
+}
+
+// Double scan: the labels of key (-1: none) re-weighted exactly, each slot's
+// entries added in CSR order by the slot's lane (val starts at 0), a run of
+// entries with scalar lane indices and no cross-lane votes.
+template <int K, class Pos>
+__device__ __forceinline__ void det_rescan(const MoveArgs &a, int x0, Pos beg, Pos end, int lane,
+                                           const int key, float &val) {
+  hub_feed(a, x0, beg, end, lane, [&](int lab, float x, int cnt) {
+    int slot = -1;
+#pragma unroll
+    for (int s = 0; s < K; ++s) slot = (lab == rl(key, s)) ? s : slot;
+    unsigned long long run = __ballot(slot >= 0 && lane < cnt && x > 0.0f);
     while (run) {
       const int h = __ffsll((long long)run) - 1;
       run &= run - 1;
@@ -509,138 +980,13 @@ __device__ __forceinline__ void add_hits(unsigned long long run, int slot, float
       const float xh = rl_f(x, h);
       val = (lane == sh) ? val + xh : val;
     }
-  }
-}
-
-// Iteration 0 from the initial labels on a row without repeated neighbours
-// (MoveArgs::fresh_hubs): every entry's label differs from every key (live
-// or stale), so every entry takes the step for a new label, and the free
-// slots change only here: they are tracked in a scalar mask, with no slot
-// lookups and no runs of hits.  The same steps as det_chain, UNIT likewise.
-template <int K, bool UNIT, class Pos>
-__device__ __forceinline__ void det_fresh(const MoveArgs &a, int x0, Pos beg, Pos end, int lane,
-                                          int &key, float &val) {
-  unsigned long long z = K >= 64 ? ~0ull : ((1ull << K) - 1ull);  // all slots free
-  hub_feed(a, x0, beg, end, lane, [&](int lab, float x, int cnt) {
-    unsigned long long pend = __ballot(lane < cnt && x > 0.0f);
-    while (pend) {
-      const int j = __ffsll((long long)pend) - 1;
-      pend &= pend - 1;
-      const int c = rl(lab, j);
-      float r;
-      if constexpr (UNIT) {
-        if (z == 0ull) {  // every slot live: each loses 1, the entry is used up
-          if (lane < K) val = val - 1.0f;
-          z = __ballot(lane < K && val == 0.0f);
-          continue;
-        }
-        r = 1.0f;
-      } else {
-        const float xw = rl_f(x, j);
-        r = xw;
-        if (z == 0ull) {  // every slot live: decrement by d = min(w, smallest slot)
-          float m = xw;
-          if constexpr (K >= 16) {
-            m = fminf(m, slot_min<K>(val, lane));
-          } else {
-#pragma unroll
-            for (int s = 0; s < K; ++s) m = fminf(m, rl_f(val, s));
-          }
-          if (lane < K) val = val - m;
-          r = xw - m;
-          z = __ballot(lane < K && val == 0.0f);
-          if (!(r > 0.0f)) continue;
-        }
-      }
-      const int s = __ffsll((long long)z) - 1;  // the lowest free slot
-      z &= z - 1;
-      key = (lane == s) ? c : key;  // selects, not a branch on the lane
-      val = (lane == s) ? r : val;
-    }
   });
 }
 
-// The sketch of one hub row in det mode after iteration 0 (see
-// hub_vertex_det), lane s < K holding slot s in key / val.  UNIT (see
-// add_hits): every slot value is an integer, so when every slot is live
-// each holds at least 1 and the entry's decrement, min(1, smallest slot),
-// is 1: every slot loses 1 and nothing is left to place.
-template <int K, bool UNIT, class Pos>
-__device__ __forceinline__ void det_chain(const MoveArgs &a, int x0, Pos beg, Pos end, int lane,
-                                          int &key, float &val) {
-  hub_feed(a, x0, beg, end, lane, [&](int lab, float x, int cnt) {
-    int slot = -1;  // the slot holding this lane's label, if any
-#pragma unroll
-    for (int s = 0; s < K; ++s) slot = (lab == rl(key, s)) ? s : slot;
-    unsigned long long pend = __ballot(lane < cnt && x > 0.0f);
-    while (pend) {
-      const unsigned long long missm = __ballot(slot < 0) & pend;
-      // entries before the first miss only add to existing slots
-      const unsigned long long run = missm ? (pend & ((missm & (~missm + 1)) - 1)) : pend;
-      pend &= ~run;
-      add_hits<UNIT>(run, slot, x, lane, val);
-      if (!missm) break;
-      const int jm = __ffsll((long long)missm) - 1;
-      pend &= ~(1ull << jm);
-      const int c = rl(lab, jm);
-      unsigned long long z = __ballot(lane < K && val == 0.0f);
-      float r;
-      if constexpr (UNIT) {
-        if (z == 0ull) {  // every slot live: each loses 1, the entry is used up
-          if (lane < K) val = val - 1.0f;
-          continue;
-        }
-        r = 1.0f;
-      } else {
-        const float xw = rl_f(x, jm);
-        r = xw;
-        if (z == 0ull) {  // every slot live: decrement by d = min(w, smallest slot)
-          float m = xw;
-          if constexpr (K >= 16) {
-            m = fminf(m, slot_min<K>(val, lane));
-          } else {
-#pragma unroll
-            for (int s = 0; s < K; ++s) m = fminf(m, rl_f(val, s));
-          }
-          if (lane < K) val = val - m;
-          r = xw - m;
-          z = r > 0.0f ? __ballot(lane < K && val == 0.0f) : 0ull;
-        }
-      }
-      if (z) {  // the (residue of the) pair takes a free slot
-        const int s = __ffsll((long long)z) - 1;
-        const int old = rl(key, s);
-        key = (lane == s) ? c : key;
-        val = (lane == s) ? r : val;
-        slot = (lab == old) ? -1 : slot;
-        slot = (lab == c) ? s : slot;
-      }
-    }
-  });
-}
-
-// Double scan: the labels of key (-1: none) re-weighted exactly, each slot's
-// entries added in CSR order by the slot's lane (val starts at 0).
-template <int K, bool UNIT, class Pos>
-__device__ __forceinline__ void det_rescan(const MoveArgs &a, int x0, Pos beg, Pos end, int lane,
-                                           const int key, float &val) {
-  hub_feed(a, x0, beg, end, lane, [&](int lab, float x, int cnt) {
-    int slot = -1;
-#pragma unroll
-    for (int s = 0; s < K; ++s) slot = (lab == rl(key, s)) ? s : slot;
-    add_hits<UNIT>(__ballot(slot >= 0 && lane < cnt && x > 0.0f), slot, x, lane, val);
-  });
-}
-
-// Lane s < K holds slot s.  For each chunk every lane first finds the slot
-// whose key equals its label (at most one: keys are unique).  Entries are
-// consumed in lane order: a run of entries whose label is already a key
-// only adds weights to those slots (add_hits); the first entry without a
-// key takes the full sketch step, after which only the lanes whose label
-// was the replaced key or is the new key change their slot.
-// p: the vertex's degree-order position.
+// One hub in det mode.  p: the vertex's degree-order position; buf: LDS of
+// this wavefront for hub_stream.
 template <int K, bool RS, class Pos>
-__device__ void hub_vertex_det(const MoveArgs &a, int p, unsigned long long &scanned,
+__device__ void hub_vertex_det(const MoveArgs &a, int *buf, int p, unsigned long long &scanned,
                                unsigned long long &changed) {
   const int lane = threadIdx.x & (kWave - 1);
   const int v = a.order[p], x0 = state_at(a, p, v);
@@ -653,29 +999,22 @@ __device__ void hub_vertex_det(const MoveArgs &a, int p, unsigned long long &sca
   const Pos beg = rfl_as(row_at<Pos>(a.row_ptr, v)), end = rfl_as(row_at<Pos>(a.row_ptr, v + 1));
   int key = -1;
   float val = 0.0f;
-  // Unit weights (see add_hits).  The double-scan kernels keep the general
-  // chains only: more copies of the chunk loop there put its chunk buffers
-  // in scratch memory.
-  const bool unit = !RS && !a.w && (long long)(end - beg) < (1ll << 24);
-  if (unit) {
-    if constexpr (!RS) {
-      if (a.fresh_hubs) {
-        det_fresh<K, true>(a, x0, beg, end, lane, key, val);
-      } else {
-        det_chain<K, true>(a, x0, beg, end, lane, key, val);
-      }
-    }
+  if (!a.w && (long long)(end - beg) < (1ll << 24)) {
+    if (a.fresh_hubs)
+      det_unit_fresh<K>(a, x0, beg, end, lane, key, val);
+    else
+      det_unit<K>(a, buf, x0, beg, end, lane, key, val);
   } else if (a.fresh_hubs) {
-    det_fresh<K, false>(a, x0, beg, end, lane, key, val);
+    det_weighted<K, true>(a, buf, x0, beg, end, lane, key, val);
   } else {
-    det_chain<K, false>(a, x0, beg, end, lane, key, val);
+    det_weighted<K, false>(a, buf, x0, beg, end, lane, key, val);
   }
   if constexpr (RS) {
     // double scan: the live slots' labels are re-weighted exactly, each
     // slot's entries added in CSR order by the slot's lane
     key = val > 0.0f ? key : -1;
     val = 0.0f;
-    det_rescan<K, false>(a, x0, beg, end, lane, key, val);
+    det_rescan<K>(a, x0, beg, end, lane, key, val);
   }
   // heaviest live slot, ties to the lowest label; keep when empty
   int bk = cv;
@@ -694,7 +1033,7 @@ __device__ void hub_vertex_det(const MoveArgs &a, int p, unsigned long long &sca
   if (lane == 0) a.Cn[x0] = moved ? c : cv;
   if (moved) {
     changed += 1;
-    mark_row(a, beg, end, lane);
+    mark_row<16>(a, beg, end, lane);
   }
   scanned += (unsigned long long)(end - beg);
 }
@@ -784,16 +1123,16 @@ __device__ void hub_vertex_det_sv(const MoveArgs &a, int p, unsigned long long &
   if (lane == 0) a.Cn[x0] = moved ? bk : cv;
   if (moved) {
     changed += 1;
-    mark_row(a, beg, end, lane);
+    mark_row<16>(a, beg, end, lane);
   }
   scanned += (unsigned long long)(end - beg);
 }
 
-// LPA_MODE_DET hub path for the vote of Algorithm 3: the vote consumes each
-// chunk in CSR order through lane reads (every lane holds the same
-// candidate).
+// LPA_MODE_DET hub path for the vote of Algorithm 3: every lane holds the
+// same candidate and takes the row's entries in CSR order (an entry of weight
+// 0 changes nothing that a later entry or the choice could tell).
 template <class Pos>
-__device__ void hub_vertex_det_bm(const MoveArgs &a, int p, unsigned long long &scanned,
+__device__ void hub_vertex_det_bm(const MoveArgs &a, int *buf, int p, unsigned long long &scanned,
                                   unsigned long long &changed) {
   const int lane = threadIdx.x & (kWave - 1);
   const int v = a.order[p], x0 = state_at(a, p, v);
@@ -806,15 +1145,13 @@ __device__ void hub_vertex_det_bm(const MoveArgs &a, int p, unsigned long long &
   const Pos beg = rfl_as(row_at<Pos>(a.row_ptr, v)), end = rfl_as(row_at<Pos>(a.row_ptr, v + 1));
   BmSketch S;
   S.clear();
-  hub_feed(a, x0, beg, end, lane, [&](int lab, float x, int cnt) {
-    for (int t = 0; t < cnt; ++t) S.add(rl(lab, t), rl_f(x, t));
-  });
+  hub_stream(a, buf, x0, beg, end, lane, [&](int c, float w) { S.add(c, w); });
   const int c = S.max_key(cv);
   const bool moved = c != cv && (!a.pickless || c < cv);
   if (lane == 0) a.Cn[x0] = moved ? c : cv;
   if (moved) {
     changed += 1;
-    mark_row(a, beg, end, lane);
+    mark_row<16>(a, beg, end, lane);
   }
   scanned += (unsigned long long)(end - beg);
 }
@@ -1101,7 +1438,8 @@ __device__ __forceinline__ void flush_last_counts(unsigned long long *dN, unsign
 template <int K, bool RS, class Pos, bool SV>
 constexpr bool kKeepCols = !RS && !SV && sizeof(Pos) == 4;
 
-template <int K, bool ASYNC, bool RS, class Pos, bool SV = false>
+// HUBS: the launch has hubs that take one wavefront each (det mode).
+template <int K, bool ASYNC, bool RS, class Pos, bool HUBS, bool SV = false>
 __device__ __forceinline__ void move_body(const Launch &L) {
   __shared__ Stage<kStageT, Pos> stage[kBlock / kWave];
   const int lane = threadIdx.x & (kWave - 1);
@@ -1126,18 +1464,19 @@ __device__ __forceinline__ void move_body(const Launch &L) {
     const MoveArgs a = make_args(d, iter);
     const int local = item - as_const(L.prefix_items)[g];
     // det mode: one wavefront per hub first; async mode has none (its hubs
-    // are cut into segments, which are lane units), so the async kernels
-    // carry no hub-chain code
+    // are cut into segments, which are lane units), and neither have det
+    // launches over graphs without hubs, so their kernels carry no hub-chain
+    // code
     int hub_items = 0;
-    if constexpr (!ASYNC) {
+    if constexpr (!ASYNC && HUBS) {
       hub_items = a.n_hubs;
       if (local < hub_items) {
         if constexpr (K == 0)
-          hub_vertex_det_bm<Pos>(a, local, scanned_w, changed_w);
+          hub_vertex_det_bm<Pos>(a, stage[wib].lab, local, scanned_w, changed_w);
         else if constexpr (SV)
           hub_vertex_det_sv<K, Pos>(a, local, scanned_w, changed_w);
         else
-          hub_vertex_det<K, RS, Pos>(a, local, scanned_w, changed_w);
+          hub_vertex_det<K, RS, Pos>(a, stage[wib].lab, local, scanned_w, changed_w);
         continue;
       }
     }
@@ -1177,23 +1516,23 @@ constexpr int kMoveWaves = W                     ? 1
                            : (K == 32 && !ASYNC) ? 3
                                                  : 1;
 
-template <int K, bool ASYNC, bool W>
+template <int K, bool ASYNC, bool W, bool HUBS>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kMoveWaves<K, ASYNC, W>)))
 void k_move(Launch L) {
-  move_body<K, ASYNC, false, PosOf<W>>(L);
+  move_body<K, ASYNC, false, PosOf<W>, HUBS>(L);
 }
 
 // ... and with the double scan (LPA_RESCAN; sketch rule only).
 template <int K, bool ASYNC, bool W>
 __global__ __launch_bounds__(kBlock) void k_move_rescan(Launch L) {
-  move_body<K, ASYNC, true, PosOf<W>>(L);
+  move_body<K, ASYNC, true, PosOf<W>, !ASYNC>(L);
 }
 
 // ... and with shared variables instead of votes in the hub path
 // (LPA_SHARED_VARS; LPA_MODE_DET, sketch rule, single scan).
 template <int K, bool W>
 __global__ __launch_bounds__(kBlock) void k_move_sv(Launch L) {
-  move_body<K, false, false, PosOf<W>, true>(L);
+  move_body<K, false, false, PosOf<W>, true, true>(L);
 }
 
 // ---------------------------------------------------------------------------
@@ -1850,8 +2189,10 @@ static hipError_t launch_t(const Launch &L, int grid, int merge_grid, hipStream_
       hipLaunchKernelGGL((k_move_rescan<K, ASYNC, W>), dim3(grid), dim3(kBlock), 0, s, L);
     else if constexpr (SV)
       hipLaunchKernelGGL((k_move_sv<K, W>), dim3(grid), dim3(kBlock), 0, s, L);
+    else if (!ASYNC && L.det_hubs > 0)
+      hipLaunchKernelGGL((k_move<K, ASYNC, W, !ASYNC>), dim3(grid), dim3(kBlock), 0, s, L);
     else
-      hipLaunchKernelGGL((k_move<K, ASYNC, W>), dim3(grid), dim3(kBlock), 0, s, L);
+      hipLaunchKernelGGL((k_move<K, ASYNC, W, false>), dim3(grid), dim3(kBlock), 0, s, L);
   }
   if (ev_end && (e = hipEventRecord(ev_end, s)) != hipSuccess) return e;
   if constexpr (HS) {  // shared hub sketches replace segments and merging
@@ -1878,7 +2219,7 @@ static hipError_t launch_t(const Launch &L, int grid, int merge_grid, hipStream_
   return hipGetLastError();
 }
 
-template <int K, bool ASYNC, bool RS, bool W, bool SV = false>
+template <int K, bool ASYNC, bool RS, bool W, bool HUBS, bool SV = false>
 static int occ_t() {
   int nb = 0;
   const void *f;
@@ -1887,7 +2228,7 @@ static int occ_t() {
   else if constexpr (SV)
     f = (const void *)k_move_sv<K, W>;
   else
-    f = (const void *)k_move<K, ASYNC, W>;
+    f = (const void *)k_move<K, ASYNC, W, HUBS && !ASYNC>;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, f, kBlock, 0) != hipSuccess) return 1;
   return nb > 0 ? nb : 1;
 }
@@ -1906,15 +2247,15 @@ static hipError_t launch_mode(int k, const Launch &L, int grid, int merge_grid, 
   }
 }
 
-template <bool ASYNC, bool RS, bool W>
+template <bool ASYNC, bool RS, bool W, bool HUBS>
 static int occ_mode(int k) {
   switch (k) {
-    case 1: return occ_t<1, ASYNC, RS, W>();
-    case 2: return occ_t<2, ASYNC, RS, W>();
-    case 4: return occ_t<4, ASYNC, RS, W>();
-    case 8: return occ_t<8, ASYNC, RS, W>();
-    case 16: return occ_t<16, ASYNC, RS, W>();
-    case 32: return occ_t<32, ASYNC, RS, W>();
+    case 1: return occ_t<1, ASYNC, RS, W, HUBS>();
+    case 2: return occ_t<2, ASYNC, RS, W, HUBS>();
+    case 4: return occ_t<4, ASYNC, RS, W, HUBS>();
+    case 8: return occ_t<8, ASYNC, RS, W, HUBS>();
+    case 16: return occ_t<16, ASYNC, RS, W, HUBS>();
+    case 32: return occ_t<32, ASYNC, RS, W, HUBS>();
     default: return 1;
   }
 }
@@ -1950,12 +2291,12 @@ static hipError_t launch_sv(int k, const Launch &L, int grid, int merge_grid, hi
 template <bool W>
 static int occ_sv(int k) {
   switch (k) {
-    case 1: return occ_t<1, false, false, W, true>();
-    case 2: return occ_t<2, false, false, W, true>();
-    case 4: return occ_t<4, false, false, W, true>();
-    case 8: return occ_t<8, false, false, W, true>();
-    case 16: return occ_t<16, false, false, W, true>();
-    case 32: return occ_t<32, false, false, W, true>();
+    case 1: return occ_t<1, false, false, W, true, true>();
+    case 2: return occ_t<2, false, false, W, true, true>();
+    case 4: return occ_t<4, false, false, W, true, true>();
+    case 8: return occ_t<8, false, false, W, true, true>();
+    case 16: return occ_t<16, false, false, W, true, true>();
+    case 32: return occ_t<32, false, false, W, true, true>();
     default: return 1;
   }
 }
@@ -1993,12 +2334,14 @@ hipError_t launch_iteration(int k, bool async_mode, bool rescan, bool hub_shared
                                           merge_grid, s, ev_beg, ev_end);
 }
 
-template <bool W>
+template <bool W, bool HUBS>
 static int move_blocks_w(int k, bool async_mode, bool rescan, bool shared_vars) {
   if (shared_vars && k > 0 && !async_mode && !rescan) return occ_sv<W>(k);
-  if (k == 0) return async_mode ? occ_t<0, true, false, W>() : occ_t<0, false, false, W>();
-  if (rescan) return async_mode ? occ_mode<true, true, W>(k) : occ_mode<false, true, W>(k);
-  return async_mode ? occ_mode<true, false, W>(k) : occ_mode<false, false, W>(k);
+  if (k == 0)
+    return async_mode ? occ_t<0, true, false, W, HUBS>() : occ_t<0, false, false, W, HUBS>();
+  if (rescan)
+    return async_mode ? occ_mode<true, true, W, HUBS>(k) : occ_mode<false, true, W, HUBS>(k);
+  return async_mode ? occ_mode<true, false, W, HUBS>(k) : occ_mode<false, false, W, HUBS>(k);
 }
 
 hipError_t launch_finish(const Launch &L, hipStream_t s) {
@@ -2007,9 +2350,13 @@ hipError_t launch_finish(const Launch &L, hipStream_t s) {
   return hipGetLastError();
 }
 
-int move_blocks_per_cu(int k, bool async_mode, bool rescan, bool shared_vars, bool wide) {
-  return wide ? move_blocks_w<true>(k, async_mode, rescan, shared_vars)
-              : move_blocks_w<false>(k, async_mode, rescan, shared_vars);
+int move_blocks_per_cu(int k, bool async_mode, bool rescan, bool shared_vars, bool wide,
+                       bool hubs) {
+  if (hubs)
+    return wide ? move_blocks_w<true, true>(k, async_mode, rescan, shared_vars)
+                : move_blocks_w<false, true>(k, async_mode, rescan, shared_vars);
+  return wide ? move_blocks_w<true, false>(k, async_mode, rescan, shared_vars)
+              : move_blocks_w<false, false>(k, async_mode, rescan, shared_vars);
 }
 
 }  // namespace lpa

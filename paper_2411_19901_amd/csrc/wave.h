@@ -71,7 +71,7 @@ struct Stage {
   P beg[kWave];  // CSR position of each row's first entry (P: offset type)
   int len[kWave];
   int self[kWave];
-  int lab[kWave * (T + 1)];
+  alignas(16) int lab[kWave * (T + 1)];
   float w[kWave * (T + 1)];
 };
 
