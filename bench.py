@@ -647,12 +647,14 @@ def main():
     if args.shared_vars:
         kname = f"lpa::k_move_sv<{kk}, {wide}>"
     else:
-        # the single-scan kernel has an instance for det launches with hubs
+        # the single-scan kernel has instances for det launches with hubs and
+        # for launches without weights
         hubs = (args.mode == "det"
                 and int((rp[1:] - rp[:-1]).max()) > (args.lane_max_degree or 4096))
+        flags = [] if args.rescan else [hubs, w is None and kk <= 8]
         kname = (f"lpa::k_move{'_rescan' if args.rescan else ''}"
                  f"<{kk}, {'true' if args.mode == 'async' else 'false'}, {wide}"
-                 f"{'' if args.rescan else ', true' if hubs else ', false'}>")
+                 + "".join(", true" if f else ", false" for f in flags) + ">")
     traffic = traffic_from_profiles(kname,
                                     workload, digest)
     result = {

@@ -415,16 +415,17 @@ struct lpa_batch {
   hipStream_t cap_stream = nullptr;  // private stream the iterations are captured on
   hipGraph_t graph = nullptr;
   hipGraphExec_t graph_exec = nullptr;
-  std::array<long long, 10> graph_key{};
+  std::array<long long, 11> graph_key{};
   bool async_mode = false;
   hipStream_t stream = nullptr;
   int device = 0;
   int check_every = 0;
   int cus = 1;
-  // resident k_move workgroups: [int32 / int64 positions][without / with det hubs]
-  int grid_cap[2][2] = {{1, 1}, {1, 1}};
+  // resident k_move workgroups (0: not asked for yet): [32- / 64-bit
+  // positions][without / with det hubs][with / without weights]
+  int grid_cap[2][2][2] = {};
   int blocks_cap = 0;        // lpa_config.move_blocks_per_cu (0: as many as fit)
-  bool wide = false;         // a loaded graph has int64 row offsets
+  bool wide = false;         // a loaded graph needs 64-bit positions (wide_positions)
   void *dblock = nullptr;  // device: descriptors, prefixes, finished counter, status
   GraphDesc *d_desc = nullptr;
   int32_t *d_prefix = nullptr;  // items, hubs, merge items, hub segments: [cap+1] each
@@ -439,7 +440,8 @@ struct lpa_batch {
   size_t off_prefix = 0, off_finished = 0, off_status = 0;
   std::vector<lpa_handle *> loaded;
   int total_items = 0, total_hubs = 0, total_merge = 0, total_segs = 0, unfinished = 0;
-  int det_hubs = 0;  // det mode: hubs of the loaded unfinished graphs
+  int det_hubs = 0;   // det mode: hubs of the loaded unfinished graphs
+  bool unit = false;  // no loaded unfinished graph has weights
   bool poisoned = false;
   std::string err;
 };
@@ -608,6 +610,13 @@ int check_k(int k, uint32_t flags) {
   if ((flags & LPA_STREAM_CSR) && (flags & (LPA_HUB_SHARED | LPA_RANKED_LAYOUT)))
     return LPA_ERR_ARG;
   return LPA_OK;
+}
+
+// Whether the move kernels need 64-bit CSR positions: int64 offsets, or arrays
+// whose byte offsets pass 2^32 (their narrow kernels address by 32-bit bytes).
+bool wide_positions(const lpa_handle *h) {
+  constexpr int64_t kNarrow = (int64_t)1 << 30;
+  return h->row_ptr.p64 != nullptr || h->nnz >= kNarrow || h->n >= kNarrow;
 }
 
 // Kernel selector: k slots, or 0 for the vote of Algorithm 3.
@@ -810,13 +819,6 @@ int batch_alloc(lpa_batch *b) {
   b->device = dev;
   if (hipDeviceGetAttribute(&b->cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return LPA_ERR_HIP;
-  for (int wide = 0; wide < 2; ++wide)
-    for (int hubs = 0; hubs < 2; ++hubs) {
-      int per_cu = move_blocks_per_cu(b->k, b->async_mode, b->rescan, b->shared_vars, wide != 0,
-                                      hubs != 0);
-      if (b->blocks_cap > 0 && b->blocks_cap < per_cu) per_cu = b->blocks_cap;
-      b->grid_cap[wide][hubs] = b->cus * per_cu;
-    }
   if (b->capture && hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking) != hipSuccess) {
     (void)hipGetLastError();
     return LPA_ERR_HIP;
@@ -845,11 +847,11 @@ int batch_load(lpa_batch *b, lpa_handle *const *hs, int count) {
   pi[0] = ph[0] = pm[0] = ps[0] = 0;
   int unfinished = 0;
   int64_t det_hubs = 0;
-  bool wide = false;
+  bool wide = false, unit = true;
   for (int g = 0; g < count; ++g) {
     lpa_handle *h = hs[g];
     if (!h) return LPA_ERR_ARG;
-    wide = wide || h->row_ptr.p64 != nullptr;
+    wide = wide || wide_positions(h);
     if (h->poisoned) return LPA_ERR_HIP;
     if (h->sm.on && b != h->self) return LPA_ERR_ARG;  // streamed graphs run alone
     if (kernel_k(h->k, h->flags) != b->k || ((h->flags & LPA_RESCAN) != 0) != b->rescan ||
@@ -863,6 +865,7 @@ int batch_load(lpa_batch *b, lpa_handle *const *hs, int count) {
     const bool live = !h->finished;
     unfinished += live ? 1 : 0;
     det_hubs += live && !b->async_mode ? h->desc.n_hubs : 0;
+    unit = unit && (!live || h->w == nullptr);
     const int64_t next[4] = {
         (int64_t)pi[g] + (live ? move_items(h) : 0),
         (int64_t)ph[g] + (live && b->async_mode ? h->desc.n_hubs : 0),
@@ -883,6 +886,7 @@ int batch_load(lpa_batch *b, lpa_handle *const *hs, int count) {
   b->unfinished = unfinished;
   b->det_hubs = (int)det_hubs;  // each is a work item: no more than total_items
   b->wide = wide;
+  b->unit = unit;
   b->loaded.assign(hs, hs + count);
   HIP_TRY_B(b, hipMemcpyAsync(b->d_desc, b->h_desc, (size_t)count * sizeof(GraphDesc),
                               hipMemcpyHostToDevice, b->stream));
@@ -905,6 +909,7 @@ Launch make_launch(lpa_batch *b) {
   L.total_merge = b->total_merge;
   L.total_segs = b->total_segs;
   L.det_hubs = b->det_hubs;
+  L.unit = b->unit ? 1 : 0;
   L.finished = b->d_finished;
   L.status_out = b->d_status;
   L.no_finish = 0;
@@ -936,7 +941,13 @@ int batch_iterate(lpa_batch *b, int iters, lpa_handle *prof) {
   const Launch L = make_launch(b);
   const int waves_per_block = kBlock / kWave;
   int grid = (b->total_items + waves_per_block - 1) / waves_per_block;
-  const int cap = b->grid_cap[b->wide][L.det_hubs > 0];
+  int &cap = b->grid_cap[b->wide][L.det_hubs > 0][b->unit];
+  if (cap == 0) {
+    int per_cu = move_blocks_per_cu(b->k, b->async_mode, b->rescan, b->shared_vars, b->wide,
+                                    L.det_hubs > 0, b->unit);
+    if (b->blocks_cap > 0 && b->blocks_cap < per_cu) per_cu = b->blocks_cap;
+    cap = b->cus * per_cu;
+  }
   if (grid > cap) grid = cap;
   if (grid < 1) grid = 1;
   int mg = (b->total_merge + waves_per_block - 1) / waves_per_block;
@@ -947,9 +958,9 @@ int batch_iterate(lpa_batch *b, int iters, lpa_handle *prof) {
     // every remaining iteration as one hipGraph, captured on a private
     // stream once per launch shape and replayed on the caller's stream
     // (the descriptor table it reads is uploaded before each replay)
-    const std::array<long long, 10> key = {iters,        grid,          mg,           L.G,
-                                           L.total_items, L.total_hubs, L.total_merge,
-                                           L.total_segs,  b->wide,      L.det_hubs > 0};
+    const std::array<long long, 11> key = {
+        iters,         grid,         mg,      L.G,            L.total_items, L.total_hubs,
+        L.total_merge, L.total_segs, b->wide, L.det_hubs > 0, b->unit};
     if (!b->graph_exec || key != b->graph_key) {
       if (b->graph_exec) (void)hipGraphExecDestroy(b->graph_exec);
       if (b->graph) (void)hipGraphDestroy(b->graph);
@@ -1311,7 +1322,7 @@ int stream_bin(lpa_handle *h) {
   S.grid_cap = cus * move_blocks_per_cu(kernel_k(h->k, h->flags), h->async_mode,
                                         (h->flags & LPA_RESCAN) != 0,
                                         (h->flags & LPA_SHARED_VARS) != 0,
-                                        h->row_ptr.p64 != nullptr, true);
+                                        wide_positions(h), true, h->w == nullptr);
   return LPA_OK;
 }
 
@@ -1351,7 +1362,7 @@ int stream_iterate(lpa_handle *h, int iters) {
   const Launch L0 = make_launch(b);
   const int kk = kernel_k(h->k, h->flags);
   const bool rescan = (h->flags & LPA_RESCAN) != 0, sv = (h->flags & LPA_SHARED_VARS) != 0;
-  const bool wide = h->row_ptr.p64 != nullptr;
+  const bool wide = wide_positions(h);
   const int waves_per_block = kBlock / kWave;
   hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, h->stream, b->d_finished, 1);
   constexpr int NB = lpa_handle::Streamed::kBufs;

@@ -159,6 +159,7 @@ struct Launch {
   int32_t total_merge;
   int32_t total_segs;
   int32_t det_hubs;         // det mode: hubs of all its graphs, one wavefront each (0: none)
+  int32_t unit;             // 1: no graph has weights
   int32_t *finished;        // graphs that have finished (counter)
   int32_t *status_out;      // [3 * G]: iter, done, dN of the iteration just run (0: none)
   int32_t no_finish;        // 1: launch_iteration leaves out the stop test (k_finish)
@@ -199,8 +200,8 @@ struct MoveArgs {
 // segments' partial sketches by one shared sketch per hub (LPA_HUB_SHARED,
 // async, k > 0, no double scan).
 // shared_vars: LPA_SHARED_VARS (det sketch rule, single scan).
-// wide: some graph of the launch has int64 row offsets (the kernels then
-// compute CSR positions in 64 bits).
+// wide: some graph of the launch has int64 row offsets, or 2^30 entries or
+// vertices (the kernels then compute CSR positions in 64 bits).
 // Enqueue one iteration of every graph in the launch (async: hub flag
 // snapshot, k_move, hub merge, and for the double scan the hub re-weighting
 // and decision; det: k_move; then the convergence test).  Non-null events
@@ -208,9 +209,10 @@ struct MoveArgs {
 hipError_t launch_iteration(int k, bool async_mode, bool rescan, bool hub_shared,
                             bool shared_vars, bool wide, const Launch &L, int grid,
                             int merge_grid, hipStream_t s, hipEvent_t ev_beg, hipEvent_t ev_end);
-// Resident workgroups of the move kernel per compute unit; hubs: of the kernel
-// for launches with det_hubs > 0.
-int move_blocks_per_cu(int k, bool async_mode, bool rescan, bool shared_vars, bool wide, bool hubs);
+// Resident workgroups per compute unit of the move kernel for launches with
+// (hubs) det_hubs > 0 and (unit) Launch::unit.
+int move_blocks_per_cu(int k, bool async_mode, bool rescan, bool shared_vars, bool wide, bool hubs,
+                       bool unit);
 // The stop test alone (k_finish): an iteration split over id ranges of a
 // graph runs launch_iteration once per range with Launch::no_finish set,
 // then this once.

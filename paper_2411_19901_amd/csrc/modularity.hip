@@ -66,8 +66,19 @@ __device__ void add_by_label(double *tot, int c, double x, bool on) {
 // together (slots past a row's end issue no load).
 constexpr int kModBatch = 4;
 
+// Staged rows: the wavefront's loads are row-contiguous (slot i * 64 + lane =
+// entry j of row r, (r, j) = (slot / TW, slot % TW)) and each lane then sums its
+// own row's weights; rows are padded to TW + 1 words against bank conflicts.
+template <int T>
+struct ModStage {
+  long long beg[kWave];
+  int len[kWave];
+  int self[kWave];  // label of the row's vertex
+  float w[kWave * (T + 1)];
+};
+
 template <int TW, int T>
-__device__ __forceinline__ void mod_step(const ModArgs &m, Stage<T, long long> &st, int lane, int t0,
+__device__ __forceinline__ void mod_step(const ModArgs &m, ModStage<T> &st, int lane, int t0,
                                          int tn, double &ki, double &in) {
   const gptr<const int32_t> col = as_global(m.col);
   const gptr<const float> wp = as_global(m.w);
@@ -113,7 +124,7 @@ __device__ __forceinline__ void mod_step(const ModArgs &m, Stage<T, long long> &
 // One lane per row: entries [beg, beg + len) of vertex v at degree-order
 // position p (v < 0: none).
 template <int T>
-__device__ void mod_lane_rows(const ModArgs &m, Stage<T, long long> &st, int lane, int p, int v,
+__device__ void mod_lane_rows(const ModArgs &m, ModStage<T> &st, int lane, int p, int v,
                               double &k_acc, double &in_acc) {
   long long beg = 0;
   int len = 0, ci = -1;
@@ -125,7 +136,7 @@ __device__ void mod_lane_rows(const ModArgs &m, Stage<T, long long> &st, int lan
   st.beg[lane] = beg;
   st.len[lane] = len;
   st.self[lane] = ci;
-  const int maxlen = rfl(wave_max(len));
+  const int maxlen = wave_max(len);
   wave_lds_sync();
   double ki = 0.0, in = 0.0;
   for (int t0 = 0; t0 < maxlen;) {
@@ -251,7 +262,7 @@ __device__ void mod_short_rows(const ModArgs &m, int q0, double &k_acc, double &
 }
 
 __global__ __launch_bounds__(kBlock) void k_modularity(ModArgs m) {
-  __shared__ Stage<kStageT, long long> stage[kBlock / kWave];  // 64-bit row positions
+  __shared__ ModStage<kStageT> stage[kBlock / kWave];
   const int lane = threadIdx.x & (kWave - 1);
   const int wib = rfl(threadIdx.x / kWave);
   const int wave = rfl(blockIdx.x * (kBlock / kWave) + wib);

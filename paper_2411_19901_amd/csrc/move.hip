@@ -53,6 +53,19 @@ __device__ __forceinline__ Pos row_at(const RowPtr &rp, int v) {
     return as_global(rp.p32)[v];
 }
 
+// Element i of an array.  Narrow positions (Pos = int: graphs of fewer than 2^30
+// entries and vertices) are byte offsets below 2^32, which loads add to a
+// scalar base: one register per address, and none of the 64-bit sums.
+template <class Pos, class T>
+__device__ __forceinline__ gptr<T> element(gptr<T> base, Pos i) {
+  if constexpr (sizeof(Pos) == 4) {
+    using Byte = typename std::conditional<std::is_const<T>::value, const char, char>::type;
+    return (gptr<T>)((gptr<Byte>)base + (unsigned)i * (unsigned)sizeof(T));
+  } else {
+    return base + i;
+  }
+}
+
 // Index of the labels and flags of the vertex at degree-order position p
 // (id v): its id, or its position when the graph keeps its state ranked.
 // The same index is what `col` holds for the vertex, so a row entry equal to
@@ -172,21 +185,28 @@ struct SketchOf<0> {
 // Slots stored per partial sketch.
 constexpr int slots_of(int K) { return K == 0 ? 1 : K; }
 
-// Load one staging step of TW entries for each of the 64 rows (TW <= T):
-// slot i * 64 + lane holds entry t0 + j of row r, (r, j) = (slot / TW,
-// slot % TW), stored at r * (TW + 1) + j.  The slots are taken kLoadBatch
-// at a time in three phases (column indices, weights, gathered labels), so
-// that each phase's loads are in flight together; a slot past its row's end
-// issues no load and is stored as padding (label -1, weight 0).  A step of
-// TW <= T / 2 leaves lab[] words 64 (TW + 1) onwards unused: with KEEP, slot
-// s's column index is kept at kept_col<TW>(s) there, for the marking pass.
-constexpr int kLoadBatch = 4;
-
+// One staging step takes TW entries (TW <= T) of each of the 64 rows.  The
+// wavefront's lanes take slots: slot i * 64 + lane holds entry t0 + j of row r,
+// (r, j) = (slot / TW, slot % TW), so a row's slots are loaded by neighbouring
+// lanes; it is stored at r * (TW + 1) + j (rows padded against bank conflicts).
+// A step of TW <= T / 2 leaves label words 64 (TW + 1) onwards unused: with
+// KEEP, slot s's column index is kept at kept_col<TW>(s) there, for the marking
+// pass.
 template <int TW>
 __device__ __forceinline__ int kept_col(int slot) { return kWave * (TW + 1) + slot; }
 
+template <int TW>
+__device__ __forceinline__ int slot_word(int r, int j) { return r * (TW + 1) + j; }
+
+// The step in four-slot batches of three phases (column indices, weights,
+// labels), so that each phase's loads are in flight together; a slot past its
+// row's end issues no load and is stored as padding (label -1, weight 0), as is
+// an entry of the vertex itself.
+constexpr int kLoadBatch = 4;
+
 template <int TW, bool KEEP, int T, class Pos>
-__device__ __forceinline__ void stage_load(const MoveArgs &a, Stage<T, Pos> &st, int lane, int t0) {
+__device__ __forceinline__ void stage_load(const MoveArgs &a, Stage<T, Pos, false> &st, int lane,
+                                           int t0) {
   constexpr int B = TW < kLoadBatch ? TW : kLoadBatch;
 #pragma unroll
   for (int i0 = 0; i0 < TW; i0 += B) {
@@ -196,73 +216,153 @@ __device__ __forceinline__ void stage_load(const MoveArgs &a, Stage<T, Pos> &st,
     float x[B];
 #pragma unroll
     for (int b = 0; b < B; ++b) {
-      const int slot = (i0 + b) * kWave + lane;
-      const int r = slot / TW, j = slot % TW;
-      ok[b] = t0 + j < st.len[r];
-      e[b] = st.beg[r] + (t0 + j);
+      const int slot = (i0 + b) * kWave + lane, r = slot / TW, j = slot % TW;
+      ok[b] = t0 + j < st.row[r].x;
+      e[b] = st.beg[r] + (Pos)(t0 + j);
     }
 #pragma unroll
-    for (int b = 0; b < B; ++b) c[b] = ok[b] ? __builtin_nontemporal_load(a.col + e[b]) : -1;
+    for (int b = 0; b < B; ++b) c[b] = ok[b] ? __builtin_nontemporal_load(element(a.col, e[b])) : -1;
 #pragma unroll
     for (int b = 0; b < B; ++b)
-      x[b] = !ok[b] ? 0.0f : (a.w ? __builtin_nontemporal_load(a.w + e[b]) : 1.0f);
+      x[b] = !ok[b] ? 0.0f : (a.w ? __builtin_nontemporal_load(element(a.w, e[b])) : 1.0f);
 #pragma unroll
-    for (int b = 0; b < B; ++b) lab[b] = ok[b] ? a.C[c[b]] : -1;
+    for (int b = 0; b < B; ++b) lab[b] = ok[b] ? *element<Pos>(a.C, c[b]) : -1;
 #pragma unroll
     for (int b = 0; b < B; ++b) {
-      const int slot = (i0 + b) * kWave + lane;
-      const int r = slot / TW, j = slot % TW;
-      st.lab[r * (TW + 1) + j] = lab[b];
-      st.w[r * (TW + 1) + j] = c[b] == st.self[r] ? 0.0f : x[b];
+      const int slot = (i0 + b) * kWave + lane, r = slot / TW, j = slot % TW;
+      st.lab[slot_word<TW>(r, j)] = lab[b];
+      st.w[slot_word<TW>(r, j)] = c[b] == st.row[r].y ? 0.0f : x[b];
       if constexpr (KEEP && 2 * TW <= T) st.lab[kept_col<TW>(slot)] = c[b];
     }
   }
 }
 
-// Feed entries [beg, beg + len) of row `self` to feed(label, weight) in CSR
-// order (len = 0: nothing); entries of the vertex itself come with weight 0.
-// All lanes of the wavefront must call it together.  Each step takes 4, 8
-// or T entries per row, the narrowest that covers what the wavefront's
-// longest row has left: with short rows a wide step would leave most load
-// slots idle.  With KEEP, returns the step width when every row fit one
-// step of width 4 or 8 (the rows' column indices are then kept in the
-// stage); otherwise 0.  Keeping them costs registers: only kernels that
-// stay within their register budget with it pass KEEP.
-template <int T, bool KEEP = false, class Pos, class Feed>
-__device__ __forceinline__ int staged_rows(const MoveArgs &a, Stage<T, Pos> &st, int lane, Pos beg,
-                                           int len, int self, Feed &&feed) {
-  st.beg[lane] = beg;
-  st.len[lane] = len;
-  st.self[lane] = self;
-  const int maxlen = rfl(wave_max(len));
-  wave_lds_sync();
-  for (int t0 = 0; t0 < maxlen;) {
-    const int rem = maxlen - t0;
-    const int tw = rem <= 4 ? 4 : (rem <= 8 ? 8 : T);
-    if (tw == 4)
-      stage_load<4, KEEP>(a, st, lane, t0);
-    else if (tw == 8)
-      stage_load<8, KEEP>(a, st, lane, t0);
-    else
-      stage_load<T, KEEP>(a, st, lane, t0);
-    wave_lds_sync();
-    // this lane's row: its first tn staged entries (later columns of the
-    // step are padding for every row: label -1, weight 0)
-    const int tn = min(tw, rem);
-    const int row = lane * (tw + 1);
-    for (int j = 0; j < tn; ++j) feed(st.lab[row + j], st.w[row + j]);
-    wave_lds_sync();
-    t0 += tw;
+// UNIT: the columns of a step go into registers, all of a lane's slots in
+// flight together, the next step's while this one is consumed; then the
+// labels, eight slots at a time.  A slot past its row's end reads the row's last
+// entry and the label of vertex 0, lines that others of the step read too, so
+// no branch stands between a step's loads: it waits for memory twice, or three
+// times for 16 entries, instead of eight times in stage_load.  Such graphs have
+// no weights to stream and rows of a few labels that hit the caches, so they
+// wait more than they move: R-MAT-22 det k = 8, iterations 0 and 8, 2.7 and 2.1
+// to 1.9 and 1.3 ms; 512 SBM graphs det k = 8 55.4 to 52.9 ms per solve (at five
+// or six wavefronts per SIMD, which this stage's LDS would allow, the spills cost
+// more: 55.9 and 59.6).
+// (With weights and labels that miss, the batches of stage_load are faster: the
+// order above cost 6% on R-MAT-24, whose columns and weights then miss L2 more
+// often, 216 against 205 million line misses in the first iteration.)
+template <int TW, class Pos, int T>
+__device__ __forceinline__ void stage_cols(const MoveArgs &a, const Stage<T, Pos, true> &st,
+                                           int lane, int t0, int (&c)[TW]) {
+#pragma unroll
+  for (int i = 0; i < TW; ++i) {
+    const int slot = i * kWave + lane, r = slot / TW, j = slot % TW;
+    const int e = min(t0 + j, max(st.row[r].x, 1) - 1);
+    c[i] = __builtin_nontemporal_load(element(a.col, st.beg[r] + (Pos)e));
   }
-  return KEEP && maxlen <= 8 && 16 <= T ? (maxlen <= 4 ? 4 : 8) : 0;
 }
 
-// Feed entries [beg, beg + len) of row `self` into S in CSR order (len = 0:
-// nothing).  All lanes of the wavefront must call it together.
-template <class SK, int T, bool KEEP = false, class Pos>
-__device__ __forceinline__ int staged_scan(const MoveArgs &a, Stage<T, Pos> &st, int lane, Pos beg,
-                                           int len, int self, SK &S) {
-  return staged_rows<T, KEEP>(a, st, lane, beg, len, self, [&](int lab, float x) { S.add(lab, x); });
+// Labels of the step's columns c into the stage; a slot past its row's end or
+// naming the vertex itself gets label -1.
+template <bool KEEP, int TW, class Pos, int T>
+__device__ __forceinline__ void stage_labels(const MoveArgs &a, Stage<T, Pos, true> &st, int lane,
+                                             int t0, const int (&c)[TW]) {
+  constexpr int B = TW < 8 ? TW : 8;
+#pragma unroll
+  for (int i0 = 0; i0 < TW; i0 += B) {
+    int lab[B];
+    unsigned on = 0;
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+      const int slot = (i0 + b) * kWave + lane, r = slot / TW, j = slot % TW;
+      const int2 row = st.row[r];
+      const bool in = t0 + j < row.x;
+      on |= in && c[i0 + b] != row.y ? 1u << b : 0u;
+      lab[b] = *element<Pos>(a.C, in ? c[i0 + b] : 0);
+    }
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+      const int slot = (i0 + b) * kWave + lane;
+      st.lab[slot_word<TW>(slot / TW, slot % TW)] = (on >> b) & 1u ? lab[b] : -1;
+      if constexpr (KEEP && 2 * TW <= T) st.lab[kept_col<TW>(slot)] = c[i0 + b];
+    }
+  }
+}
+
+// Feed entries [beg, beg + len) of row `self` to feed(label, weight) in CSR
+// order (len = 0: nothing); entries of the vertex itself and past the row's
+// end come with weight 0.  All lanes of the wavefront must call it together.
+// Each step takes 4, 8 or T entries per row, the narrowest that covers what
+// the wavefront's longest row has left: with short rows a wide step would
+// leave most load slots idle.  With KEEP, returns the step width when every
+// row fit one step of width 4 or 8 (the rows' column indices are then kept in
+// the stage); otherwise 0.  Keeping them costs registers: only kernels that
+// stay within their register budget with it pass KEEP.
+template <bool KEEP, int T, class Pos, bool UNIT, class Feed>
+__device__ __forceinline__ int staged_rows(const MoveArgs &a, Stage<T, Pos, UNIT> &st, int lane,
+                                           Pos beg, int len, int self, Feed &&feed) {
+  static_assert(T == 16, "step widths 4, 8 and 16");
+  st.beg[lane] = beg;
+  st.row[lane] = make_int2(len, self);
+  const int maxlen = wave_max(len);
+  if (maxlen == 0) return 0;
+  wave_lds_sync();
+  int t0 = 0;
+  // this lane's row: its first entries of a step of tw staged ones (later
+  // columns of the step are past the end of every row)
+  const auto consume = [&](int tw) {
+    wave_lds_sync();
+    const int tn = min(tw, maxlen - t0);
+    const int row = lane * (tw + 1);
+    for (int j = 0; j < tn; ++j) {
+      const int lab = st.lab[row + j];
+      if constexpr (UNIT)
+        feed(lab, lab >= 0 ? 1.0f : 0.0f);
+      else
+        feed(lab, st.w[row + j]);
+    }
+    wave_lds_sync();
+    t0 += tw;
+  };
+  if constexpr (UNIT) {
+    if (maxlen > 8) {
+      int c[T];
+      stage_cols(a, st, lane, 0, c);
+      for (;;) {
+        stage_labels<KEEP>(a, st, lane, t0, c);
+        const bool more = maxlen - (t0 + T) > 8;
+        if (more) stage_cols(a, st, lane, t0 + T, c);
+        consume(T);
+        if (!more) break;
+      }
+    }
+    if (t0 < maxlen) {
+      if (maxlen - t0 <= 4) {
+        int c[4];
+        stage_cols(a, st, lane, t0, c);
+        stage_labels<KEEP>(a, st, lane, t0, c);
+        consume(4);
+      } else {
+        int c[8];
+        stage_cols(a, st, lane, t0, c);
+        stage_labels<KEEP>(a, st, lane, t0, c);
+        consume(8);
+      }
+    }
+  } else {
+    while (t0 < maxlen) {
+      const int rem = maxlen - t0;
+      const int tw = rem <= 4 ? 4 : (rem <= 8 ? 8 : T);
+      if (tw == 4)
+        stage_load<4, KEEP>(a, st, lane, t0);
+      else if (tw == 8)
+        stage_load<8, KEEP>(a, st, lane, t0);
+      else
+        stage_load<T, KEEP>(a, st, lane, t0);
+      consume(tw);
+    }
+  }
+  return KEEP && maxlen <= 8 ? (maxlen <= 4 ? 4 : 8) : 0;
 }
 
 // Double scan (Section 4.4, Algorithm 4 rescan): the live slots of the
@@ -305,17 +405,16 @@ __device__ __forceinline__ void mark(const MoveArgs &a, int j) { a.act_next[j] =
 // Mark the neighbours of every lane whose `moved` is set (entries [beg, beg +
 // len) of its row), with row-contiguous column loads by the whole wavefront:
 // all of a step's column loads are issued before its flag stores.
-template <int TW, int T, class Pos>
-__device__ __forceinline__ void mark_step(const MoveArgs &a, const Stage<T, Pos> &st, int lane,
-                                          int t0) {
+template <int TW, class Pos, class St>
+__device__ __forceinline__ void mark_step(const MoveArgs &a, const St &st, int lane, int t0) {
   bool ok[TW];
   int c[TW];
 #pragma unroll
   for (int i = 0; i < TW; ++i) {
     const int slot = i * kWave + lane;
     const int r = slot / TW, j = slot % TW;
-    ok[i] = t0 + j < st.len[r];
-    c[i] = ok[i] ? __builtin_nontemporal_load(a.col + (st.beg[r] + (t0 + j))) : 0;
+    ok[i] = t0 + j < st.row[r].x;
+    c[i] = ok[i] ? __builtin_nontemporal_load(element(a.col, st.beg[r] + (Pos)(t0 + j))) : 0;
   }
 #pragma unroll
   for (int i = 0; i < TW; ++i)
@@ -344,52 +443,49 @@ __device__ __forceinline__ void mark_row(const MoveArgs &a, Pos beg, Pos end, in
   }
 }
 
-// Mark from the column indices a single scan step of width TW kept in the
-// stage: each lane takes the slots it loaded (st.len already holds 0 for
-// rows that did not move).
-template <int TW, int T, class Pos>
-__device__ __forceinline__ void mark_kept(const MoveArgs &a, const Stage<T, Pos> &st, int lane) {
+// Mark from the columns that a single staging step of width TW kept in the
+// stage: each lane takes the slots it loaded (st.row already holds no entries
+// for rows that did not move).
+template <int TW, class St>
+__device__ __forceinline__ void mark_kept(const MoveArgs &a, const St &st, int lane) {
 #pragma unroll
   for (int i = 0; i < TW; ++i) {
-    const int slot = i * kWave + lane;
-    const int r = slot / TW, j = slot % TW;
-    if (j < st.len[r]) mark(a, st.lab[kept_col<TW>(slot)]);
+    const int slot = i * kWave + lane, r = slot / TW, j = slot % TW;
+    if (j < st.row[r].x) mark(a, st.lab[kept_col<TW>(slot)]);
   }
 }
 
 // Mark the neighbours of every lane whose `moved` is set (entries [beg, beg +
 // len) of its row), with row-contiguous column loads by the whole wavefront
 // and the same step widths as staged_rows.  kept = the width staged_rows
-// returned for these rows (the stage then still holds their column indices
-// and nothing is read from the CSR), or 0.
-template <int T, class Pos>
-__device__ __forceinline__ void staged_mark(const MoveArgs &a, Stage<T, Pos> &st, int lane, Pos beg,
-                                            int len, bool moved, int kept) {
+// returned for these rows (the stage then still holds their columns and
+// nothing is read from the CSR), or 0.
+template <int T, class Pos, bool UNIT>
+__device__ __forceinline__ void staged_mark(const MoveArgs &a, Stage<T, Pos, UNIT> &st, int lane,
+                                            Pos beg, int len, bool moved, int kept) {
   if (__ballot(moved) == 0ull) return;
   st.beg[lane] = beg;
-  st.len[lane] = moved ? len : 0;
-  const int maxlen = rfl(wave_max(moved ? len : 0));
+  st.row[lane].x = moved ? len : 0;
+  const int maxlen = wave_max(moved ? len : 0);
   wave_lds_sync();
-  if (kept == 4) {
-    mark_kept<4>(a, st, lane);
-    wave_lds_sync();
-    return;
-  }
-  if (kept == 8) {
-    mark_kept<8>(a, st, lane);
+  if (kept != 0) {
+    if (kept == 4)
+      mark_kept<4>(a, st, lane);
+    else
+      mark_kept<8>(a, st, lane);
     wave_lds_sync();
     return;
   }
   for (int t0 = 0; t0 < maxlen;) {
     const int rem = maxlen - t0;
     if (rem <= 4) {
-      mark_step<4>(a, st, lane, t0);
+      mark_step<4, Pos>(a, st, lane, t0);
       t0 += 4;
     } else if (rem <= 8) {
-      mark_step<8>(a, st, lane, t0);
+      mark_step<8, Pos>(a, st, lane, t0);
       t0 += 8;
     } else {
-      mark_step<T>(a, st, lane, t0);
+      mark_step<T, Pos>(a, st, lane, t0);
       t0 += T;
     }
   }
@@ -1161,8 +1257,13 @@ __device__ void hub_vertex_det_bm(const MoveArgs &a, int *buf, int p, unsigned l
 // hub h = seg_hub[u] (async only); otherwise whole vertex order[n_hubs + u -
 // n_seg].
 // ---------------------------------------------------------------------------
-template <int K, bool ASYNC, bool RS, class Pos, bool KEEP>
-__device__ __forceinline__ void lane_units(const MoveArgs &a, Stage<kStageT, Pos> &st, int u,
+// The stage keeps a step's columns for marking in the kernels whose wavefronts
+// per SIMD it leaves unchanged.
+template <int K, bool RS, class Pos, bool SV>
+constexpr bool kKeepCols = !RS && !SV && sizeof(Pos) == 4;
+
+template <int K, bool ASYNC, bool RS, class Pos, bool SV, bool UNIT>
+__device__ __forceinline__ void lane_units(const MoveArgs &a, Stage<kStageT, Pos, UNIT> &st, int u,
                                            unsigned long long &scanned,
                                            unsigned long long &changed) {
   const int lane = threadIdx.x & (kWave - 1);
@@ -1195,7 +1296,9 @@ __device__ __forceinline__ void lane_units(const MoveArgs &a, Stage<kStageT, Pos
   if (!active) len = 0;
   typename SketchOf<K>::type S;
   S.clear();
-  const int kept = staged_scan<typename SketchOf<K>::type, kStageT, KEEP>(a, st, lane, beg, len, sx, S);
+  constexpr bool KEEP = kKeepCols<K, RS, Pos, SV>;
+  int kept = staged_rows<KEEP>(a, st, lane, beg, len, sx,
+                               [&](int lab, float x) { S.add(lab, x); });
   scanned += (unsigned long long)len;
   int c = cv;
   if constexpr (RS) {
@@ -1203,8 +1306,8 @@ __device__ __forceinline__ void lane_units(const MoveArgs &a, Stage<kStageT, Pos
     // their sketches are merged (k_hub_rescan)
     Rescan<K> R;
     R.from(S);
-    staged_rows<kStageT>(a, st, lane, beg, whole ? len : 0, sx,
-                         [&](int lab, float x) { R.add(lab, x); });
+    kept = staged_rows<KEEP>(a, st, lane, beg, whole ? len : 0, sx,
+                             [&](int lab, float x) { R.add(lab, x); });
     if (whole) c = R.best(cv);
   } else {
     if (whole) c = S.max_key(cv);
@@ -1229,7 +1332,7 @@ __device__ __forceinline__ void lane_units(const MoveArgs &a, Stage<kStageT, Pos
   }
   // every lane reaches here: the marking pass is wavefront-cooperative
   changed += (unsigned long long)__popcll(__ballot(moved));
-  staged_mark<kStageT>(a, st, lane, beg, len, moved, kept);
+  staged_mark(a, st, lane, beg, len, moved, kept);
 }
 
 // ---------------------------------------------------------------------------
@@ -1429,19 +1532,11 @@ __device__ __forceinline__ void flush_last_counts(unsigned long long *dN, unsign
   scanned_lane = scanned_w = changed_w = 0;
 }
 
-// Lane units keep narrow rows' column indices in the stage for marking
-// (staged_rows) only in the kernels whose wavefronts per SIMD it leaves
-// unchanged: single scan, sketch votes, 32-bit positions (k <= 8 stays
-// within 128 registers, k = 16 within 168, k = 32 within 256).  In the
-// 64-bit, double-scan and shared-variable kernels the extra registers would
-// cost a wavefront per SIMD, which the gathers need more.
-template <int K, bool RS, class Pos, bool SV>
-constexpr bool kKeepCols = !RS && !SV && sizeof(Pos) == 4;
-
-// HUBS: the launch has hubs that take one wavefront each (det mode).
-template <int K, bool ASYNC, bool RS, class Pos, bool HUBS, bool SV = false>
+// HUBS: the launch has hubs that take one wavefront each (det mode).  UNIT: no
+// graph of the launch has weights.
+template <int K, bool ASYNC, bool RS, class Pos, bool HUBS, bool UNIT, bool SV = false>
 __device__ __forceinline__ void move_body(const Launch &L) {
-  __shared__ Stage<kStageT, Pos> stage[kBlock / kWave];
+  __shared__ Stage<kStageT, Pos, UNIT> stage[kBlock / kWave];
   const int lane = threadIdx.x & (kWave - 1);
   const int wib = rfl(threadIdx.x / kWave);
   const int wave = rfl(blockIdx.x * (kBlock / kWave) + wib);
@@ -1461,7 +1556,8 @@ __device__ __forceinline__ void move_body(const Launch &L) {
       cdN = d.dN + iter;
       csc = d.scanned + iter;
     }
-    const MoveArgs a = make_args(d, iter);
+    MoveArgs a = make_args(d, iter);
+    if constexpr (UNIT) a.w = nullptr;
     const int local = item - as_const(L.prefix_items)[g];
     // det mode: one wavefront per hub first; async mode has none (its hubs
     // are cut into segments, which are lane units), and neither have det
@@ -1492,15 +1588,16 @@ __device__ __forceinline__ void move_body(const Launch &L) {
         continue;
       }
     }
-    lane_units<K, ASYNC, RS, Pos, kKeepCols<K, RS, Pos, SV>>(
+    lane_units<K, ASYNC, RS, Pos, SV, UNIT>(
         a, stage[wib], lane_local * kWave + lane, scanned_lane, changed_w);
   }
   flush_last_counts(cdN, csc, scanned_lane, scanned_w, changed_w, wib);
 }
 
-// CSR positions are int for graphs of fewer than 2^31 entries (W = false),
-// long long otherwise (W = true, which also reads int32 offsets): 32-bit
-// positions keep one register per staged load address.
+// CSR positions are int for graphs of int32 offsets and fewer than 2^30 entries
+// and vertices (W = false), long long otherwise (W = true, which also reads
+// int32 offsets): positions whose byte offsets fit 32 bits keep one register
+// per load address (element).
 template <bool W>
 using PosOf = typename std::conditional<W, long long, int>::type;
 
@@ -1516,23 +1613,23 @@ constexpr int kMoveWaves = W                     ? 1
                            : (K == 32 && !ASYNC) ? 3
                                                  : 1;
 
-template <int K, bool ASYNC, bool W, bool HUBS>
+template <int K, bool ASYNC, bool W, bool HUBS, bool UNIT>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kMoveWaves<K, ASYNC, W>)))
 void k_move(Launch L) {
-  move_body<K, ASYNC, false, PosOf<W>, HUBS>(L);
+  move_body<K, ASYNC, false, PosOf<W>, HUBS, UNIT>(L);
 }
 
 // ... and with the double scan (LPA_RESCAN; sketch rule only).
 template <int K, bool ASYNC, bool W>
 __global__ __launch_bounds__(kBlock) void k_move_rescan(Launch L) {
-  move_body<K, ASYNC, true, PosOf<W>, !ASYNC>(L);
+  move_body<K, ASYNC, true, PosOf<W>, !ASYNC, false>(L);
 }
 
 // ... and with shared variables instead of votes in the hub path
 // (LPA_SHARED_VARS; LPA_MODE_DET, sketch rule, single scan).
 template <int K, bool W>
 __global__ __launch_bounds__(kBlock) void k_move_sv(Launch L) {
-  move_body<K, false, false, PosOf<W>, true, true>(L);
+  move_body<K, false, false, PosOf<W>, true, false, true>(L);
 }
 
 // ---------------------------------------------------------------------------
@@ -2174,6 +2271,18 @@ __global__ void k_finish(Launch L) {
   }
 }
 
+// The single-scan move kernel of a launch (see move_body): its instances leave
+// out what no graph of the launch needs.  With 16 or more slots the registers do
+// not hold the wider loads of the unit-weight staging (k = 16 spilled 33 at
+// four wavefronts per SIMD), so those take the general instance.
+template <int K, bool ASYNC, bool W>
+static auto move_kernel(bool hubs, bool unit) -> void (*)(Launch) {
+  constexpr bool U = K <= 8;
+  if (!ASYNC && hubs)
+    return unit && U ? k_move<K, ASYNC, W, !ASYNC, U> : k_move<K, ASYNC, W, !ASYNC, false>;
+  return unit && U ? k_move<K, ASYNC, W, false, U> : k_move<K, ASYNC, W, false, false>;
+}
+
 // ---------------------------------------------------------------------------
 template <int K, bool ASYNC, bool RS, bool W, bool HS = false, bool SV = false>
 static hipError_t launch_t(const Launch &L, int grid, int merge_grid, hipStream_t s,
@@ -2189,10 +2298,9 @@ static hipError_t launch_t(const Launch &L, int grid, int merge_grid, hipStream_
       hipLaunchKernelGGL((k_move_rescan<K, ASYNC, W>), dim3(grid), dim3(kBlock), 0, s, L);
     else if constexpr (SV)
       hipLaunchKernelGGL((k_move_sv<K, W>), dim3(grid), dim3(kBlock), 0, s, L);
-    else if (!ASYNC && L.det_hubs > 0)
-      hipLaunchKernelGGL((k_move<K, ASYNC, W, !ASYNC>), dim3(grid), dim3(kBlock), 0, s, L);
     else
-      hipLaunchKernelGGL((k_move<K, ASYNC, W, false>), dim3(grid), dim3(kBlock), 0, s, L);
+      hipLaunchKernelGGL((move_kernel<K, ASYNC, W>(L.det_hubs > 0, L.unit != 0)), dim3(grid),
+                         dim3(kBlock), 0, s, L);
   }
   if (ev_end && (e = hipEventRecord(ev_end, s)) != hipSuccess) return e;
   if constexpr (HS) {  // shared hub sketches replace segments and merging
@@ -2219,8 +2327,8 @@ static hipError_t launch_t(const Launch &L, int grid, int merge_grid, hipStream_
   return hipGetLastError();
 }
 
-template <int K, bool ASYNC, bool RS, bool W, bool HUBS, bool SV = false>
-static int occ_t() {
+template <int K, bool ASYNC, bool RS, bool W, bool SV = false>
+static int occ_t(bool hubs, bool unit) {
   int nb = 0;
   const void *f;
   if constexpr (RS)
@@ -2228,7 +2336,7 @@ static int occ_t() {
   else if constexpr (SV)
     f = (const void *)k_move_sv<K, W>;
   else
-    f = (const void *)k_move<K, ASYNC, W, HUBS && !ASYNC>;
+    f = (const void *)move_kernel<K, ASYNC, W>(hubs, unit);
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, f, kBlock, 0) != hipSuccess) return 1;
   return nb > 0 ? nb : 1;
 }
@@ -2247,15 +2355,15 @@ static hipError_t launch_mode(int k, const Launch &L, int grid, int merge_grid, 
   }
 }
 
-template <bool ASYNC, bool RS, bool W, bool HUBS>
-static int occ_mode(int k) {
+template <bool ASYNC, bool RS, bool W>
+static int occ_mode(int k, bool hubs, bool unit) {
   switch (k) {
-    case 1: return occ_t<1, ASYNC, RS, W, HUBS>();
-    case 2: return occ_t<2, ASYNC, RS, W, HUBS>();
-    case 4: return occ_t<4, ASYNC, RS, W, HUBS>();
-    case 8: return occ_t<8, ASYNC, RS, W, HUBS>();
-    case 16: return occ_t<16, ASYNC, RS, W, HUBS>();
-    case 32: return occ_t<32, ASYNC, RS, W, HUBS>();
+    case 1: return occ_t<1, ASYNC, RS, W>(hubs, unit);
+    case 2: return occ_t<2, ASYNC, RS, W>(hubs, unit);
+    case 4: return occ_t<4, ASYNC, RS, W>(hubs, unit);
+    case 8: return occ_t<8, ASYNC, RS, W>(hubs, unit);
+    case 16: return occ_t<16, ASYNC, RS, W>(hubs, unit);
+    case 32: return occ_t<32, ASYNC, RS, W>(hubs, unit);
     default: return 1;
   }
 }
@@ -2291,12 +2399,12 @@ static hipError_t launch_sv(int k, const Launch &L, int grid, int merge_grid, hi
 template <bool W>
 static int occ_sv(int k) {
   switch (k) {
-    case 1: return occ_t<1, false, false, W, true, true>();
-    case 2: return occ_t<2, false, false, W, true, true>();
-    case 4: return occ_t<4, false, false, W, true, true>();
-    case 8: return occ_t<8, false, false, W, true, true>();
-    case 16: return occ_t<16, false, false, W, true, true>();
-    case 32: return occ_t<32, false, false, W, true, true>();
+    case 1: return occ_t<1, false, false, W, true>(true, false);
+    case 2: return occ_t<2, false, false, W, true>(true, false);
+    case 4: return occ_t<4, false, false, W, true>(true, false);
+    case 8: return occ_t<8, false, false, W, true>(true, false);
+    case 16: return occ_t<16, false, false, W, true>(true, false);
+    case 32: return occ_t<32, false, false, W, true>(true, false);
     default: return 1;
   }
 }
@@ -2334,14 +2442,17 @@ hipError_t launch_iteration(int k, bool async_mode, bool rescan, bool hub_shared
                                           merge_grid, s, ev_beg, ev_end);
 }
 
-template <bool W, bool HUBS>
-static int move_blocks_w(int k, bool async_mode, bool rescan, bool shared_vars) {
+template <bool W>
+static int move_blocks_w(int k, bool async_mode, bool rescan, bool shared_vars, bool hubs,
+                         bool unit) {
   if (shared_vars && k > 0 && !async_mode && !rescan) return occ_sv<W>(k);
   if (k == 0)
-    return async_mode ? occ_t<0, true, false, W, HUBS>() : occ_t<0, false, false, W, HUBS>();
+    return async_mode ? occ_t<0, true, false, W>(hubs, unit) : occ_t<0, false, false, W>(hubs, unit);
   if (rescan)
-    return async_mode ? occ_mode<true, true, W, HUBS>(k) : occ_mode<false, true, W, HUBS>(k);
-  return async_mode ? occ_mode<true, false, W, HUBS>(k) : occ_mode<false, false, W, HUBS>(k);
+    return async_mode ? occ_mode<true, true, W>(k, hubs, unit)
+                      : occ_mode<false, true, W>(k, hubs, unit);
+  return async_mode ? occ_mode<true, false, W>(k, hubs, unit)
+                    : occ_mode<false, false, W>(k, hubs, unit);
 }
 
 hipError_t launch_finish(const Launch &L, hipStream_t s) {
@@ -2350,13 +2461,10 @@ hipError_t launch_finish(const Launch &L, hipStream_t s) {
   return hipGetLastError();
 }
 
-int move_blocks_per_cu(int k, bool async_mode, bool rescan, bool shared_vars, bool wide,
-                       bool hubs) {
-  if (hubs)
-    return wide ? move_blocks_w<true, true>(k, async_mode, rescan, shared_vars)
-                : move_blocks_w<false, true>(k, async_mode, rescan, shared_vars);
-  return wide ? move_blocks_w<true, false>(k, async_mode, rescan, shared_vars)
-              : move_blocks_w<false, false>(k, async_mode, rescan, shared_vars);
+int move_blocks_per_cu(int k, bool async_mode, bool rescan, bool shared_vars, bool wide, bool hubs,
+                       bool unit) {
+  return wide ? move_blocks_w<true>(k, async_mode, rescan, shared_vars, hubs, unit)
+              : move_blocks_w<false>(k, async_mode, rescan, shared_vars, hubs, unit);
 }
 
 }  // namespace lpa

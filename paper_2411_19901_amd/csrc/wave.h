@@ -49,10 +49,14 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
+// Largest x of the wavefront's lanes, as a scalar: within each 16-lane row by
+// lane moves, then over the rows.
 __device__ __forceinline__ int wave_max(int x) {
-#pragma unroll
-  for (int off = kWave / 2; off >= 1; off >>= 1) x = max(x, __shfl_xor(x, off));
-  return x;
+  x = max(x, dpp<0xB1>(x));   // quad: lanes 1, 0, 3, 2
+  x = max(x, dpp<0x4E>(x));   // quad: lanes 2, 3, 0, 1
+  x = max(x, dpp<0x141>(x));  // mirrored half rows
+  x = max(x, dpp<0x140>(x));  // mirrored rows
+  return max(max(rl(x, 0), rl(x, 16)), max(rl(x, 32), rl(x, 48)));
 }
 
 __device__ __forceinline__ double wave_sum_d(double x) {
@@ -61,21 +65,19 @@ __device__ __forceinline__ double wave_sum_d(double x) {
   return x;
 }
 
-// LDS staging of 64 rows (one per lane), T entries per row per step: the
-// wavefront loads slot i * 64 + lane = entry j of row r with (r, j) =
-// (slot / T, slot % T), so its loads are row-contiguous; each lane then
-// reads its own row back.  Rows are padded to T + 1 words against bank
-// conflicts.
-template <int T, class P = int>
+// LDS staging of 64 rows (one per lane), T entries per row per step (see
+// slot_word in move.hip for which word holds which entry).  UNIT: of graphs
+// without weights, half the LDS.
+template <int T, class P, bool UNIT>
 struct Stage {
-  P beg[kWave];  // CSR position of each row's first entry (P: offset type)
-  int len[kWave];
-  int self[kWave];
+  P beg[kWave];     // CSR position of each row's first entry (P: offset type)
+  int2 row[kWave];  // x: entries of the row, y: its vertex's own index in col
   alignas(16) int lab[kWave * (T + 1)];
-  float w[kWave * (T + 1)];
+  float w[UNIT ? 4 : kWave * (T + 1)];
 };
 
-// Entries per row per staging step (LDS per wavefront: 64 x 17 x 8 bytes).
+// Entries per row per staging step (LDS per wavefront: 64 x 17 x 8 bytes, 64 x
+// 17 x 4 for unit weights).
 constexpr int kStageT = 16;
 
 }  // namespace lpa
