@@ -193,6 +193,10 @@ __global__ void k_scan_sums(unsigned *sums, int nchunks, const unsigned *x, int 
   totals[0] = (int)hubs;
   totals[1] = (int)(placed - hubs);
   totals[3] = (int)(placed - (short_first > hubs ? short_first : hubs));
+  // lane vertices of more than kLaneExact entries lie before the exact classes
+  const size_t e = (size_t)(kHubClasses + kLaneBuckets) * nblk;
+  const unsigned exact_first = x[e] + sums[e / kScanChunk];
+  totals[4] = (int)(exact_first > hubs ? exact_first - hubs : 0);
 }
 
 __global__ void k_scan_add(unsigned *x, size_t count, const unsigned *sums) {
@@ -472,6 +476,7 @@ struct lpa_handle {
   uint32_t *hist = nullptr;  // binning scratch
   int32_t seg_cap = 0, hub_cap = 0;
   int32_t n_segs = 0;  // hub segments planned (det mode too, for modularity)
+  int32_t n_mid = 0;   // lane vertices of more than kLaneExact entries (for modularity)
   double *mod_tot = nullptr;
   int mod_grid = 0;  // k_modularity workgroups (resident on every CU)
   double *mod_acc = nullptr;
@@ -1108,9 +1113,10 @@ namespace {
 // (before the labels are initialised) and synchronising once for the
 // totals.
 hipError_t bin_range(lpa_handle *h, int v0, int nr, int32_t *order, int *hubs, int *lanes,
-                     int *shorts = nullptr) {
+                     int *shorts = nullptr, int *mids = nullptr) {
   *hubs = *lanes = 0;
   if (shorts) *shorts = 0;
+  if (mids) *mids = 0;
   if (nr <= 0) return hipSuccess;
   const int nblk = (nr + kBinIds - 1) / kBinIds;
   const size_t cells = (size_t)kBinClasses * nblk;
@@ -1128,7 +1134,7 @@ hipError_t bin_range(lpa_handle *h, int v0, int nr, int32_t *order, int *hubs, i
                      h->lane_max, nblk, (const unsigned *)counts, order);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  int totals[4] = {0, 0, 0, 0};
+  int totals[5] = {0, 0, 0, 0, 0};
   if ((e = hipMemcpyAsync(totals, h->st->totals, sizeof(totals), hipMemcpyDeviceToHost,
                           h->stream)) != hipSuccess ||
       (e = hipStreamSynchronize(h->stream)) != hipSuccess)
@@ -1136,6 +1142,7 @@ hipError_t bin_range(lpa_handle *h, int v0, int nr, int32_t *order, int *hubs, i
   *hubs = totals[0];
   *lanes = totals[1];
   if (shorts) *shorts = totals[3];
+  if (mids) *mids = totals[4];
   return hipSuccess;
 }
 
@@ -1559,7 +1566,7 @@ int lpa_init(const lpa_graph *g, const float *weights, int k, double tol, int ma
   // degree binning (once per graph)
   if (n > 0) {
     int hubs = 0, lanes = 0, shorts = 0;
-    if (bin_range(h, 0, n, (int32_t *)d.order, &hubs, &lanes, &shorts) != hipSuccess)
+    if (bin_range(h, 0, n, (int32_t *)d.order, &hubs, &lanes, &shorts, &h->n_mid) != hipSuccess)
       return bail(LPA_ERR_HIP);
     d.n_hubs = hubs;
     d.n_lane = lanes;
@@ -1873,6 +1880,7 @@ int modularity_into(lpa_handle *h, const int32_t *labels, double *q, double *tot
   m.n_hubs = d.n_hubs;
   m.n_lane = d.n_lane;
   m.n_short = d.n_short;
+  m.n_mid = h->n_mid;
   // hubs are read segment by segment (one wavefront per segment) when the
   // handle planned its segments; otherwise one wavefront per hub
   m.n_seg = h->sm.on ? 0 : h->n_segs;

@@ -100,7 +100,9 @@ struct GraphStatus {
   int32_t iter;       // iterations run so far
   int32_t done;       // converged or max_iter reached
   int32_t err;        // validation / label-check error bits
-  int32_t totals[4];  // binning results: hubs, lane vertices, segments, short vertices
+  // binning results: hubs, lane vertices, segments, short vertices, lane
+  // vertices of more than kLaneExact entries
+  int32_t totals[5];
   int32_t fresh;      // 1: the labels are the initial ones (reset, no lpa_set_state since)
   unsigned long long sink;
 };
@@ -220,8 +222,9 @@ hipError_t launch_finish(const Launch &L, hipStream_t s);
 
 // Modularity of one labelling (Eq. 1): vertices order[0, n_hubs) are read
 // by one wavefront per segment (or per hub without segments),
-// order[n_hubs, n_hubs + n_lane) one lane each (the last n_short of them,
-// rows of at most kShortDeg entries, kShortRows rows per lane).
+// order[n_hubs, n_hubs + n_mid) by one wavefront each, the other lane vertices
+// one lane each (the last n_short of them, rows of at most kShortDeg entries,
+// kShortRows rows per lane).
 // Labels must lie in [0, n).  acc[0] += 2m, acc[1] += sigma,
 // tot[c] += K_i for every vertex i labelled c.
 struct ModArgs {
@@ -229,6 +232,7 @@ struct ModArgs {
   int32_t n_hubs;
   int32_t n_lane;
   int32_t n_short;
+  int32_t n_mid;  // the first n_mid lane vertices: more than kLaneExact entries
   RowPtr row_ptr;
   const int32_t *col;  // ranked: degree-order positions of the neighbours
   const float *w;

@@ -7,34 +7,64 @@
 // k_modularity accumulates 2m and sigma and scatters K_i into Sigma_c; the
 // square sum is taken by a second pass over Sigma (in capi.hip).
 //
-// Same decomposition as the move kernels: vertices above the binning
-// threshold are read by one wavefront each (coalesced), the others one lane
-// per row with the rows staged through LDS so the wavefront's loads are
-// row-contiguous.  The labels are only read, so no ordering is needed.
+// Vertices above the binning threshold are read segment by segment and rows of
+// more than kLaneExact entries one by one, by a whole wavefront (coalesced);
+// the others one lane per row with the rows staged through LDS so the
+// wavefront's loads are row-contiguous.  The labels are only read, so no
+// ordering is needed.
 #include "lpa_internal.h"
 #include "wave.h"
 
 namespace lpa {
 namespace {
 
-// tot[c] += x for every lane where `on` holds.  The lanes that share the
-// lowest active lane's label are summed across the wavefront and added
-// with one atomic (a converged labelling often gives most of a wavefront's
-// vertices one community, whose atomics on one address would serialise);
-// the other lanes are summed per run of consecutive lanes with one label
-// (vertices close in the degree order are often neighbours, so a label
-// tends to come in runs) and each run's first lane adds its sum.
-__device__ void add_by_label(double *tot, int c, double x, bool on) {
+// Part of Sigma_label that this wavefront has not added to the totals yet, one
+// sum per lane: the label that most of its recent vertices carry (-1: none).
+struct Held {
+  int label;
+  double sum;
+};
+
+__device__ __forceinline__ void flush_held(double *tot, Held &held) {
+  if (held.label < 0) return;
+  const double s = wave_sum_d(held.sum);
+  if ((threadIdx.x & (kWave - 1)) == 0) atomicAdd(&tot[held.label], s);
+}
+
+// tot[c] += x for every lane where `on` holds.  Atomics on one address
+// serialise, and a converged labelling gives half of a graph's vertices one
+// label, so the wavefront keeps its lanes' parts of one label (held) and adds
+// them once it ends or another label becomes more frequent: the lanes that
+// share the lowest or the highest other lane's label take its place when they
+// are at least 8 and more than the lanes of the held one.  Otherwise the lowest
+// lane's are summed across the wavefront and added with one atomic; the other
+// lanes are summed per run of consecutive lanes with one label (vertices close
+// in the degree order are often neighbours, so a label tends to come in runs)
+// and each run's first lane adds its sum.  R-MAT-23 with half of the vertices
+// in one community: 8.7 ms per call without the held label, 2.9 with it (4096^2
+// grid, the same labels: 27 and 0.7; labellings without such a community are
+// unchanged).
+__device__ void add_by_label(double *tot, int c, double x, bool on, Held &held) {
   const int lane = threadIdx.x & (kWave - 1);
-  unsigned long long rest = __ballot(on);
+  const bool kept = on && c == held.label;
+  held.sum += kept ? x : 0.0;
+  const int nheld = (int)__popcll(__ballot(kept));
+  unsigned long long rest = __ballot(on && !kept);
   if (!rest) return;
   {
     const int src = __ffsll((long long)rest) - 1;
-    const int cs = rl(c, src);
-    const bool grp = on && c == cs;
-    const unsigned long long gm = __ballot(grp);
-    if (gm & (gm - 1)) {  // two or more lanes
-      const double s = wave_sum_d(grp ? x : 0.0);
+    const int cs = rl(c, src), ct = rl(c, 63 - __clzll((long long)rest));
+    const unsigned long long gm = __ballot(on && c == cs), hm = __ballot(on && c == ct);
+    const int most = (int)max(__popcll(gm), __popcll(hm));
+    if (most >= 8 && most > nheld) {
+      flush_held(tot, held);
+      const bool low = __popcll(gm) == most;
+      held.label = low ? cs : ct;
+      const unsigned long long mm = low ? gm : hm;
+      held.sum = (mm >> lane) & 1ull ? x : 0.0;
+      rest &= ~mm;
+    } else if (gm & (gm - 1)) {  // two or more lanes
+      const double s = wave_sum_d((gm >> lane) & 1ull ? x : 0.0);
       if (lane == src) atomicAdd(&tot[cs], s);
       rest &= ~gm;
     }
@@ -125,7 +155,7 @@ __device__ __forceinline__ void mod_step(const ModArgs &m, ModStage<T> &st, int 
 // position p (v < 0: none).
 template <int T>
 __device__ void mod_lane_rows(const ModArgs &m, ModStage<T> &st, int lane, int p, int v,
-                              double &k_acc, double &in_acc) {
+                              double &k_acc, double &in_acc, Held &held) {
   long long beg = 0;
   int len = 0, ci = -1;
   if (v >= 0) {
@@ -155,14 +185,14 @@ __device__ void mod_lane_rows(const ModArgs &m, ModStage<T> &st, int lane, int p
   if (!m.w) ki = (double)len;
   k_acc += ki;
   in_acc += in;
-  add_by_label(m.tot, ci, ki, v >= 0 && len > 0);
+  add_by_label(m.tot, ci, ki, v >= 0 && len > 0, held);
 }
 
 // One wavefront per hub segment: entries [rb, re) of the row of vertex v
-// at degree-order position p; (pc, ps) is this wavefront's pending
-// contribution to Sigma_pc, flushed when the label changes.
+// at degree-order position p; its weight goes to the wavefront's held label,
+// which is flushed when the label changes.
 __device__ void mod_hub(const ModArgs &m, int p, int v, long long rb, long long re,
-                        double &k_acc, double &in_acc, int &pc, double &ps) {
+                        double &k_acc, double &in_acc, Held &held) {
   const int lane = threadIdx.x & (kWave - 1);
   const gptr<const int32_t> col = as_global(m.col);
   const gptr<const float> wp = as_global(m.w);
@@ -194,13 +224,35 @@ __device__ void mod_hub(const ModArgs &m, int p, int v, long long rb, long long 
   }
   k_acc += ki;
   in_acc += in;
-  const double kv = wave_sum_d(ki);
-  if (ci != pc) {
-    if (pc >= 0 && lane == 0) atomicAdd(&m.tot[pc], ps);
-    pc = ci;
-    ps = 0.0;
+  if (ci != held.label) {
+    flush_held(m.tot, held);
+    held = {ci, 0.0};
   }
-  ps += kv;
+  held.sum += ki;
+}
+
+// Rows of more than kLaneExact entries, the first n_mid lane vertices, kMidRows
+// to a wavefront's item, read whole by the wavefront one after another: with one
+// lane per row the longest rows of a wavefront set its time, 16 entries per
+// step and a wait for memory in each (R-MAT-20 and -23, rows up to 4096: 2.9 ms
+// per call whatever their size; read like this 0.3 and 2.1 ms).
+// p0: position of the item's first row; rows: at most kMidRows.
+constexpr int kMidRows = 4;
+
+__device__ void mod_mid_rows(const ModArgs &m, int p0, int rows, double &k_acc, double &in_acc,
+                             Held &held) {
+  int v[kMidRows];
+  long long rb[kMidRows], re[kMidRows];
+#pragma unroll
+  for (int r = 0; r < kMidRows; ++r) v[r] = m.order[p0 + min(r, rows - 1)];
+#pragma unroll
+  for (int r = 0; r < kMidRows; ++r) {
+    rb[r] = m.row_ptr[v[r]];
+    re[r] = r < rows ? m.row_ptr[v[r] + 1] : rb[r];
+  }
+#pragma unroll
+  for (int r = 0; r < kMidRows; ++r)
+    if (r < rows) mod_hub(m, p0 + r, v[r], rb[r], re[r], k_acc, in_acc, held);
 }
 
 // Short rows (degree 1 .. kShortDeg, the last n_short lane vertices): each
@@ -208,7 +260,8 @@ __device__ void mod_hub(const ModArgs &m, int p, int v, long long rb, long long 
 // weights and labels loaded phase by phase, as the move kernels' short units
 // do; such rows are bound by their dependent loads, not by bandwidth.
 // q0: index of the first row among the short ones.
-__device__ void mod_short_rows(const ModArgs &m, int q0, double &k_acc, double &in_acc) {
+__device__ void mod_short_rows(const ModArgs &m, int q0, double &k_acc, double &in_acc,
+                               Held &held) {
   constexpr int R = kShortRows, D = kShortDeg;
   const int lane = threadIdx.x & (kWave - 1);
   const int p0 = m.n_hubs + m.n_lane - m.n_short;
@@ -257,7 +310,7 @@ __device__ void mod_short_rows(const ModArgs &m, int q0, double &k_acc, double &
     }
     k_acc += ki;
     in_acc += in;
-    add_by_label(m.tot, ci[r], ki, v[r] >= 0 && len[r] > 0);
+    add_by_label(m.tot, ci[r], ki, v[r] >= 0 && len[r] > 0, held);
   }
 }
 
@@ -269,11 +322,13 @@ __global__ __launch_bounds__(kBlock) void k_modularity(ModArgs m) {
   const int nwaves = gridDim.x * (kBlock / kWave);
   // hub items: one per segment, or one per whole hub without segments
   const int hub_items = m.n_seg > 0 ? m.n_seg : m.n_hubs;
-  const int lane_rows = m.n_lane - m.n_short;  // staged lane rows, then the short ones
+  const int mid_items = (m.n_mid + kMidRows - 1) / kMidRows;
+  // staged lane rows, then the short ones
+  const int first_row = m.n_hubs + m.n_mid, lane_rows = m.n_lane - m.n_mid - m.n_short;
   const int row_items = (lane_rows + kWave - 1) / kWave;
-  const int items = hub_items + (int)lane_items(m.n_lane, m.n_short);
-  double k_acc = 0.0, in_acc = 0.0, ps = 0.0;
-  int pc = -1;
+  const int items = hub_items + mid_items + (int)lane_items(m.n_lane - m.n_mid, m.n_short);
+  double k_acc = 0.0, in_acc = 0.0;
+  Held held = {-1, 0.0};
   for (int item = wave; item < items; item += nwaves) {
     if (item < hub_items) {
       int h = item;
@@ -286,16 +341,20 @@ __global__ __launch_bounds__(kBlock) void k_modularity(ModArgs m) {
       const long long rb = m.row_ptr[v], re = m.row_ptr[v + 1];
       const long long b = m.n_seg > 0 ? rb + q * m.seg_len : rb;
       const long long e = m.n_seg > 0 ? min(b + (long long)m.seg_len, re) : re;
-      mod_hub(m, h, v, b, e, k_acc, in_acc, pc, ps);
-    } else if (item - hub_items < row_items) {
-      const int u = (item - hub_items) * kWave + lane;
-      const int v = u < lane_rows ? m.order[m.n_hubs + u] : -1;
-      mod_lane_rows<kStageT>(m, stage[wib], lane, m.n_hubs + u, v, k_acc, in_acc);
+      mod_hub(m, h, v, b, e, k_acc, in_acc, held);
+    } else if (item - hub_items < mid_items) {
+      const int u = (item - hub_items) * kMidRows;
+      mod_mid_rows(m, m.n_hubs + u, min(kMidRows, m.n_mid - u), k_acc, in_acc, held);
+    } else if (item - hub_items - mid_items < row_items) {
+      const int u = (item - hub_items - mid_items) * kWave + lane;
+      const int v = u < lane_rows ? m.order[first_row + u] : -1;
+      mod_lane_rows<kStageT>(m, stage[wib], lane, first_row + u, v, k_acc, in_acc, held);
     } else {
-      mod_short_rows(m, (item - hub_items - row_items) * (kWave * kShortRows), k_acc, in_acc);
+      mod_short_rows(m, (item - hub_items - mid_items - row_items) * (kWave * kShortRows), k_acc,
+                     in_acc, held);
     }
   }
-  if (pc >= 0 && lane == 0) atomicAdd(&m.tot[pc], ps);
+  flush_held(m.tot, held);
   // one pair of atomics per workgroup: atomics on the two accumulators
   // serialise, so the workgroup sums its wavefronts' parts first
   __shared__ double part[2][kBlock / kWave];
