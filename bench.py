@@ -642,6 +642,8 @@ def main():
 
     achieved = kernel_bytes / (kernel_ms * 1e-3) / 1e9 if kernel_ms > 0 else 0.0
     digest = source_digest()
+    lane_max = args.lane_max_degree or (1024 if args.mode == "async"
+                                        else 768 if g.nnz < 1 << 24 else 2048)
     kk = args.k if args.rule == "mg" else 0  # kernel template: 0 = the vote of Algorithm 3
     wide = "true" if args.offsets64 else "false"
     if args.shared_vars:
@@ -649,8 +651,7 @@ def main():
     else:
         # the single-scan kernel has instances for det launches with hubs and
         # for launches without weights
-        hubs = (args.mode == "det"
-                and int((rp[1:] - rp[:-1]).max()) > (args.lane_max_degree or 4096))
+        hubs = args.mode == "det" and int((rp[1:] - rp[:-1]).max()) > lane_max
         flags = [] if args.rescan else [hubs, w is None and kk <= 8]
         kname = (f"lpa::k_move{'_rescan' if args.rescan else ''}"
                  f"<{kk}, {'true' if args.mode == 'async' else 'false'}, {wide}"
@@ -671,8 +672,7 @@ def main():
         "dtype": "f32",
         "data": "synthetic",
         "config": {"workload": workload, "n": g.n, "nnz": g.nnz, "k": args.k, "rule": args.rule,
-                   "lane_max_degree": args.lane_max_degree or (1024 if args.mode == "async"
-                                                                else 4096),
+                   "lane_max_degree": lane_max,
                    "rescan": args.rescan, "offsets": 64 if args.offsets64 else 32,
                    "ranked_layout": bool(args.ranked),
                    "move_blocks_per_cu": args.move_blocks_per_cu,

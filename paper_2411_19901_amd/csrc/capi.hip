@@ -633,10 +633,18 @@ int check_ready(lpa_handle *h) {
   return LPA_OK;
 }
 
-// Longest run of CSR entries one lane scans (measured on R-MAT scale 24).
-// Lane threshold S when the caller leaves it 0: the autotuner's choice on
-// R-MAT scale 22-24 (async 1024, det 4096); tune.py picks per graph.
-int default_lane_max(bool async_mode) { return async_mode ? 1024 : 4096; }
+// Lane threshold S when the caller leaves it 0.  Async: 1024, the autotuner's
+// choice on R-MAT scale 22-24.  Det: rows above S run as one chain per
+// wavefront, and the longest rows a lane takes set the time of its wavefront;
+// a chain takes some 35 ns per entry, a lane 500.  Large graphs have a hub whose
+// chain is longer than any lane row, and more chains beside it slow it (R-MAT-21
+// weighted k = 4, ms per solve at S = 768 / 2048 / 4096: 21.4 / 20.3 / 20.3,
+// R-MAT-20 weighted k = 8: 13.4 / 13.0 / 16.3); on small ones the lane rows are
+// what lasts (R-MAT-17: 3.6 / 4.6 / 10.2).  tune.py picks S per graph.
+int default_lane_max(bool async_mode, int64_t nnz) {
+  if (async_mode) return 1024;
+  return nnz < (int64_t)1 << 24 ? 768 : 2048;
+}
 
 // labels after the iterations run so far
 int32_t *cur_labels(const lpa_handle *h) { return h->desc.C[h->iter & 1]; }
@@ -1097,7 +1105,7 @@ int lpa_workspace_bytes(int32_t n, int64_t nnz, int k, int max_iter, const lpa_c
   if (rc) return rc;
   if ((rc = check_k(k, cfg.flags)) != LPA_OK) return rc;
   const bool async_mode = (cfg.flags & LPA_MODE_MASK) == LPA_MODE_ASYNC;
-  const int lane_max = cfg.lane_max_degree > 0 ? cfg.lane_max_degree : default_lane_max(async_mode);
+  const int lane_max = cfg.lane_max_degree > 0 ? cfg.lane_max_degree : default_lane_max(async_mode, nnz);
   const Layout Ly = plan_layout(n, nnz, k, max_iter, async_mode, lane_max,
                                 (cfg.flags & LPA_RESCAN) != 0, true,
                                 (cfg.flags & LPA_RANKED_LAYOUT) != 0);
@@ -1486,7 +1494,7 @@ int lpa_init(const lpa_graph *g, const float *weights, int k, double tol, int ma
   h->async_mode = (cfg.flags & LPA_MODE_MASK) == LPA_MODE_ASYNC;
   h->seed = seed;
   h->check_every = cfg.check_every;
-  h->lane_max = cfg.lane_max_degree > 0 ? cfg.lane_max_degree : default_lane_max(h->async_mode);
+  h->lane_max = cfg.lane_max_degree > 0 ? cfg.lane_max_degree : default_lane_max(h->async_mode, h->nnz);
   auto bail = [&](int code) {
     lpa_free(h);
     return code;
