@@ -24,16 +24,6 @@ namespace {
 constexpr int kAuxBlock = 256;
 constexpr int kPrefixArrays = 4;  // per-graph prefix sums kept for a batched launch
 
-__global__ void k_fill_i32_iota(int32_t *C, int n) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) C[i] = i;
-}
-
-// Ranked layout: labels start as the ids of the vertices at each position.
-__global__ void k_copy_i32(const int32_t *src, int32_t *dst, int n) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-    dst[i] = src[i];
-}
-
 // pos[order[p]] = p: the degree-order position of every vertex.
 __global__ void k_positions(const int32_t *order, int n, int32_t *pos) {
   for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < n; p += gridDim.x * blockDim.x)
@@ -64,12 +54,6 @@ __global__ void k_fill_u8(uint8_t *p, size_t count, uint8_t v) {
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < count;
        i += (size_t)gridDim.x * blockDim.x)
     p[i] = v;
-}
-
-__global__ void k_fill_u64(unsigned long long *p, size_t count) {
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < count;
-       i += (size_t)gridDim.x * blockDim.x)
-    p[i] = 0ull;
 }
 
 __global__ void k_normalize_u8(uint8_t *p, int n) {
@@ -366,33 +350,55 @@ __global__ __launch_bounds__(256) void k_check_hub_rows(const int32_t *order, co
   if (__ballot(b != 0) != 0ull && lane == 0) atomicOr(bad, 1);
 }
 
-// lpa_reset of every graph of a table: blockIdx.y (strided) picks the graph,
-// the x blocks stride over its vertices; block x = 0 also clears the
-// per-iteration counters and the status.
-__global__ void k_batch_reset(const GraphDesc *d, int G) {
-  for (int g = blockIdx.y; g < G; g += gridDim.y) {
-    const GraphDesc &gd = d[g];
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < gd.n; i += gridDim.x * blockDim.x) {
-      const int c = gd.ranked ? gd.order[i] : i;  // the id of the vertex whose label this is
-      gd.C[0][i] = c;
-      if (gd.C[1] != gd.C[0]) gd.C[1][i] = c;
-      gd.act[0][i] = 1;
-      if (gd.act[1] != gd.act[0]) gd.act[1][i] = 0;
-    }
-    if (blockIdx.x == 0) {
-      const int T = gd.max_iter > 0 ? gd.max_iter : 1;
-      for (int t = threadIdx.x; t < T; t += blockDim.x) {
-        gd.dN[t] = 0;
-        gd.scanned[t] = 0;
-      }
-      if (threadIdx.x == 0) {
-        gd.st->iter = 0;
-        gd.st->done = (gd.n == 0 || gd.max_iter == 0) ? 1 : 0;
-        gd.st->err = 0;
-        gd.st->fresh = 1;
-      }
+// Iteration-0 state of one graph (Algorithm 1, lpa): labels are vertex ids,
+// every vertex is unprocessed; the x blocks stride over its vertices, four to a
+// thread, and block x = 0 also clears the per-iteration counters and the
+// status.
+__device__ __forceinline__ void reset_graph(const GraphDesc &gd) {
+  const int n4 = gd.n / 4, stride = gridDim.x * blockDim.x;
+  const bool two = gd.C[1] != gd.C[0];
+  const uchar4 one4 = make_uchar4(1, 1, 1, 1), zero4 = make_uchar4(0, 0, 0, 0);
+  for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < n4; q += stride) {
+    // ranked: the label at position p is the id of the vertex there
+    const int4 c = gd.ranked ? reinterpret_cast<const int4 *>(gd.order)[q]
+                             : make_int4(4 * q, 4 * q + 1, 4 * q + 2, 4 * q + 3);
+    reinterpret_cast<int4 *>(gd.C[0])[q] = c;
+    reinterpret_cast<uchar4 *>(gd.act[0])[q] = one4;
+    if (two) {
+      reinterpret_cast<int4 *>(gd.C[1])[q] = c;
+      reinterpret_cast<uchar4 *>(gd.act[1])[q] = zero4;
     }
   }
+  if (blockIdx.x == 0) {
+    const int i = 4 * n4 + (int)threadIdx.x;
+    if (i < gd.n) {
+      const int c = gd.ranked ? gd.order[i] : i;
+      gd.C[0][i] = c;
+      gd.act[0][i] = 1;
+      if (two) {
+        gd.C[1][i] = c;
+        gd.act[1][i] = 0;
+      }
+    }
+    const int T = gd.max_iter > 0 ? gd.max_iter : 1;
+    for (int t = threadIdx.x; t < T; t += blockDim.x) {
+      gd.dN[t] = 0;
+      gd.scanned[t] = 0;
+    }
+    if (threadIdx.x == 0) {
+      gd.st->iter = 0;
+      gd.st->done = (gd.n == 0 || gd.max_iter == 0) ? 1 : 0;
+      gd.st->err = 0;
+      gd.st->fresh = 1;
+    }
+  }
+}
+
+__global__ __launch_bounds__(kAuxBlock) void k_reset(GraphDesc gd) { reset_graph(gd); }
+
+// lpa_reset of every graph of a table: blockIdx.y (strided) picks the graph.
+__global__ __launch_bounds__(kAuxBlock) void k_batch_reset(const GraphDesc *d, int G) {
+  for (int g = blockIdx.y; g < G; g += gridDim.y) reset_graph(d[g]);
 }
 
 __global__ void k_status_clear_err(GraphStatus *st) {
@@ -490,6 +496,7 @@ struct lpa_batch {
   GraphDesc *d_desc = nullptr;
   int32_t *d_prefix = nullptr;  // items, hubs, merge items, hub segments: [cap+1] each
   int32_t *d_finished = nullptr;
+  uint32_t *d_ticket = nullptr;
   int32_t *d_status = nullptr;  // [3 * cap]: iter, done, dN of the last launched iteration
   void *hblock = nullptr;  // pinned host mirror of the same layout
   GraphDesc *h_desc = nullptr;
@@ -777,30 +784,10 @@ Layout plan_layout(int32_t n, int64_t nnz, int k, int max_iter, bool async_mode,
 
 // Enqueue iteration-0 state.
 int enqueue_reset(lpa_handle *h) {
-  const int n = h->n;
-  const size_t T = (size_t)(h->max_iter > 0 ? h->max_iter : 1);
-  if (n > 0) {
-    for (int b = 0; b < 2; ++b) {
-      if (b == 1 && h->desc.C[1] == h->desc.C[0]) break;
-      if (h->desc.ranked)  // label at position p: the id of the vertex there
-        hipLaunchKernelGGL(k_copy_i32, dim3(grid_for(n)), dim3(kAuxBlock), 0, h->stream,
-                           h->desc.order, h->desc.C[b], n);
-      else
-        hipLaunchKernelGGL(k_fill_i32_iota, dim3(grid_for(n)), dim3(kAuxBlock), 0, h->stream,
-                           h->desc.C[b], n);
-    }
-    hipLaunchKernelGGL(k_fill_u8, dim3(grid_for(n)), dim3(kAuxBlock), 0, h->stream, h->desc.act[0],
-                       (size_t)n, (uint8_t)1);
-    if (h->desc.act[1] != h->desc.act[0])
-      hipLaunchKernelGGL(k_fill_u8, dim3(grid_for(n)), dim3(kAuxBlock), 0, h->stream,
-                         h->desc.act[1], (size_t)n, (uint8_t)0);
-  }
-  hipLaunchKernelGGL(k_fill_u64, dim3(grid_for(T)), dim3(kAuxBlock), 0, h->stream, h->desc.dN, T);
-  hipLaunchKernelGGL(k_fill_u64, dim3(grid_for(T)), dim3(kAuxBlock), 0, h->stream,
-                     h->desc.scanned, T);
-  const bool done0 = (n == 0 || h->max_iter == 0);
-  hipLaunchKernelGGL(k_status_set, dim3(1), dim3(64), 0, h->stream, h->st, 0, done0 ? 1 : 0, 1);
-  LAUNCH_TRY(h, "reset kernels");
+  const bool done0 = (h->n == 0 || h->max_iter == 0);
+  hipLaunchKernelGGL(k_reset, dim3(grid_for((size_t)h->n / 4 + 1)), dim3(kAuxBlock), 0, h->stream,
+                     h->desc);
+  LAUNCH_TRY(h, "reset kernel");
   h->iter = 0;
   h->finished = done0;
   std::fill(h->ev_rec.begin(), h->ev_rec.end(), (uint8_t)0);
@@ -864,7 +851,7 @@ int batch_alloc(lpa_batch *b) {
   b->off_prefix = off;
   off = align_up(off + kPrefixArrays * (cap + 1) * sizeof(int32_t));
   b->off_finished = off;
-  off = align_up(off + sizeof(int32_t));
+  off += 4 * sizeof(int32_t);  // the finished counter and the stop test's ticket
   b->off_status = off;
   off = align_up(off + 3 * cap * sizeof(int32_t));
   b->block_bytes = off;
@@ -884,6 +871,8 @@ int batch_alloc(lpa_batch *b) {
   b->d_finished = (int32_t *)(d + b->off_finished);
   b->h_finished = (int32_t *)(hh + b->off_finished);
   b->d_status = (int32_t *)(d + b->off_status);
+  b->d_ticket = (uint32_t *)(b->d_finished + 1);
+  memset(hh + b->off_finished, 0, b->off_status - b->off_finished);
   b->h_status = (int32_t *)(hh + b->off_status);
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return LPA_ERR_HIP;
@@ -959,11 +948,19 @@ int batch_load(lpa_batch *b, lpa_handle *const *hs, int count) {
   b->wide = wide;
   b->unit = unit;
   b->loaded.assign(hs, hs + count);
-  HIP_TRY_B(b, hipMemcpyAsync(b->d_desc, b->h_desc, (size_t)count * sizeof(GraphDesc),
-                              hipMemcpyHostToDevice, b->stream));
-  HIP_TRY_B(b, hipMemcpyAsync(b->d_prefix, b->h_prefix,
-                              kPrefixArrays * (b->capacity + 1) * sizeof(int32_t),
-                              hipMemcpyHostToDevice, b->stream));
+  // descriptors, prefix sums, finished counter (0) and ticket (0) lie in one
+  // piece: one copy where the unused descriptors between them are few
+  constexpr size_t kOneCopy = 64 << 10;
+  const size_t desc_bytes = (size_t)count * sizeof(GraphDesc);
+  memset(b->h_finished, 0, b->off_status - b->off_finished);
+  if (b->off_prefix - desc_bytes <= kOneCopy) {
+    HIP_TRY_B(b, hipMemcpyAsync(b->dblock, b->hblock, b->off_status, hipMemcpyHostToDevice,
+                                b->stream));
+  } else {
+    HIP_TRY_B(b, hipMemcpyAsync(b->d_desc, b->h_desc, desc_bytes, hipMemcpyHostToDevice, b->stream));
+    HIP_TRY_B(b, hipMemcpyAsync(b->d_prefix, b->h_prefix, b->off_status - b->off_prefix,
+                                hipMemcpyHostToDevice, b->stream));
+  }
   return LPA_OK;
 }
 
@@ -984,17 +981,18 @@ Launch make_launch(lpa_batch *b) {
   L.finished = b->d_finished;
   L.status_out = b->d_status;
   L.no_finish = 0;
+  L.fuse_finish = 0;
+  L.ticket = b->d_ticket;
   return L;
 }
 
 // Read the status of every loaded graph back into the handles.
 int batch_read_status(lpa_batch *b) {
   const int G = (int)b->loaded.size();
-  if (G > 0)
-    HIP_TRY_B(b, hipMemcpyAsync(b->h_status, b->d_status, 3 * (size_t)G * sizeof(int32_t),
-                                hipMemcpyDeviceToHost, b->stream));
-  HIP_TRY_B(b, hipMemcpyAsync(b->h_finished, b->d_finished, sizeof(int32_t), hipMemcpyDeviceToHost,
-                              b->stream));
+  // the finished counter and the statuses lie in one piece
+  HIP_TRY_B(b, hipMemcpyAsync(b->h_finished, b->d_finished,
+                              b->off_status - b->off_finished + 3 * (size_t)G * sizeof(int32_t),
+                              hipMemcpyDeviceToHost, b->stream));
   HIP_TRY_B(b, hipStreamSynchronize(b->stream));
   for (int g = 0; g < G; ++g) {
     lpa_handle *h = b->loaded[g];
@@ -1057,8 +1055,7 @@ int batch_iterate(lpa_batch *b, int iters, lpa_handle *prof) {
     HIP_TRY_B(b, hipGraphLaunch(b->graph_exec, b->stream));
     return LPA_OK;
   }
-  hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, b->stream, b->d_finished, 1);
-  for (int i = 0; i < iters; ++i) {
+  for (int i = 0; i < iters; ++i) {  // the finished counter starts at 0 (batch_load)
     hipEvent_t eb = nullptr, ee = nullptr;
     if (prof && !prof->ev_beg.empty()) {
       const int l = prof->iter + i;
@@ -1437,7 +1434,6 @@ int stream_iterate(lpa_handle *h, int iters) {
   const bool rescan = (h->flags & LPA_RESCAN) != 0, sv = (h->flags & LPA_SHARED_VARS) != 0;
   const bool wide = wide_positions(h);
   const int waves_per_block = kBlock / kWave;
-  hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, h->stream, b->d_finished, 1);
   constexpr int NB = lpa_handle::Streamed::kBufs;
   for (int i = 0; i < iters && !h->finished; ++i) {
     const int l = h->iter;
@@ -1751,7 +1747,6 @@ int lpa_step(lpa_handle *h, int64_t *changed, int *done) {
     if (done) *done = 1;
     return LPA_OK;
   }
-  const int l = h->iter;
   lpa_batch *b = h->self;
   lpa_handle *one[1] = {h};
   if (h->sm.on) {
@@ -1760,10 +1755,8 @@ int lpa_step(lpa_handle *h, int64_t *changed, int *done) {
     if ((rc = batch_load(b, one, 1)) != LPA_OK) return batch_error_to_handles(b, rc);
     if ((rc = batch_iterate(b, 1, h)) != LPA_OK) return batch_error_to_handles(b, rc);
   }
-  unsigned long long dn = 0;
-  HIP_TRY(h, hipMemcpyAsync(&dn, h->desc.dN + l, sizeof(dn), hipMemcpyDeviceToHost, h->stream));
-  if ((rc = batch_read_status(b)) != LPA_OK) return batch_error_to_handles(b, rc);
-  if (changed) *changed = (int64_t)dn;
+  if (!h->sm.on && (rc = batch_read_status(b)) != LPA_OK) return batch_error_to_handles(b, rc);
+  if (changed) *changed = (int64_t)b->h_status[2];  // the stop test wrote dN there
   if (done) *done = h->finished ? 1 : 0;
   return LPA_OK;
 }
@@ -1826,7 +1819,7 @@ int lpa_batch_reset(lpa_batch *b, lpa_handle *const *hs, int count) {
   if (count == 0) return LPA_OK;
   int maxn = 1;
   for (int g = 0; g < count; ++g) maxn = hs[g]->n > maxn ? hs[g]->n : maxn;
-  const int gx = grid_for((size_t)maxn, kAuxBlock, 1024);
+  const int gx = grid_for((size_t)maxn / 4 + 1, kAuxBlock, 1024);
   const int gy = count < 65535 ? count : 65535;
   hipLaunchKernelGGL(k_batch_reset, dim3(gx, gy), dim3(kAuxBlock), 0, b->stream, b->d_desc, count);
   const hipError_t e = hipGetLastError();
