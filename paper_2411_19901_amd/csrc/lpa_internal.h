@@ -71,9 +71,9 @@ __host__ __device__ __forceinline__ gptr<T> as_global(T *p) {
   return (gptr<T>)p;
 }
 
-// Launch tables that no kernel writes while it runs (the per-graph prefix
-// sums and descriptors, and each graph's status outside the stop test,
-// which writes it in a launch of its own): typed as the constant address
+// Launch tables that no kernel writes while it reads them (the per-graph prefix
+// sums and descriptors, and each graph's status outside the stop test, which
+// writes it in a launch of its own or when every workgroup has read it): typed as the constant address
 // space, so that reads at uniform addresses are scalar loads served by the
 // scalar cache rather than vector-memory round trips.
 #define LPA_CONST __attribute__((address_space(4)))

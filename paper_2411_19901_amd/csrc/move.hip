@@ -1439,8 +1439,9 @@ __device__ __forceinline__ int find_graph(const int32_t *prefix_, int G, int ite
   return lo;
 }
 
-// Status of graph g for the kernels other than the stop test (k_finish, the
-// only writer, runs in a launch of its own), through the scalar cache.
+// Status of graph g for all but the stop test, through the scalar cache: the
+// stop test, its only writer, runs when every workgroup has read it (finish_last)
+// or in a launch of its own (k_finish).
 __device__ __forceinline__ kptr<GraphStatus> status_of(const Launch &L, int g) {
   return as_const(as_const(L.d)[g].st);
 }
@@ -1656,10 +1657,13 @@ using PosOf = typename std::conditional<W, long long, int>::type;
 // kernel is held to 128 registers up to k = 16, which keeps four wavefronts
 // per SIMD for the gathers (async k = 16 spills a few registers there and
 // still runs 8% faster on R-MAT-24 than with three wavefronts), and to 168
-// for k = 32 in det mode (three); the other instantiations are left to the
-// compiler.
+// for k = 32 in det mode (three).  So are the det kernels of 64-bit positions
+// up to k = 8 (the 4096^2 grid with int64 offsets: 6.76 to 6.46 ms per solve;
+// R-MAT-21: 21.9 to 21.2 ms); the async ones lose by it (R-MAT-22, unit
+// weights, k = 8: 8.88 to 9.10 ms per solve) and the other instantiations are
+// left to the compiler.
 template <int K, bool ASYNC, bool W>
-constexpr int kMoveWaves = W                     ? 1
+constexpr int kMoveWaves = W                     ? (K <= 8 && !ASYNC ? 4 : 1)
                            : (K <= 16)           ? 4
                            : (K == 32 && !ASYNC) ? 3
                                                  : 1;
