@@ -642,8 +642,9 @@ def main():
 
     achieved = kernel_bytes / (kernel_ms * 1e-3) / 1e9 if kernel_ms > 0 else 0.0
     digest = source_digest()
-    lane_max = args.lane_max_degree or (1024 if args.mode == "async"
-                                        else 768 if g.nnz < 1 << 24 else 2048)
+    det_default = next((s for e, s in ((18, 64), (20, 128), (21, 256), (24, 768))
+                        if g.nnz < 1 << e), 2048)
+    lane_max = args.lane_max_degree or (1024 if args.mode == "async" else det_default)
     kk = args.k if args.rule == "mg" else 0  # kernel template: 0 = the vote of Algorithm 3
     wide = "true" if args.offsets64 else "false"
     if args.shared_vars:

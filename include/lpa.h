@@ -184,8 +184,9 @@ typedef struct lpa_config {
   int32_t lane_max_degree; /* vertices with degree <= this run one lane per
                               vertex, higher degrees cooperatively;
                               0 = default for the mode and the graph's
-                              entries (async 1024; det 768 below 2^24
-                              entries, else 2048).  Never changes
+                              entries (async 1024; det 64 below 2^18
+                              entries, 128 below 2^20, 256 below 2^21, 768
+                              below 2^24, else 2048).  Never changes
                               LPA_MODE_DET results. */
   int32_t check_every;     /* lpa_run / lpa_batch_run read the convergence
                               state on the host every this many iterations

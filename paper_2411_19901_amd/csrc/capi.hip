@@ -699,13 +699,21 @@ int check_ready(lpa_handle *h) {
 // Lane threshold S when the caller leaves it 0.  Async: 1024, the autotuner's
 // choice on R-MAT scale 22-24.  Det: rows above S run as one chain per
 // wavefront, and the longest rows a lane takes set the time of its wavefront;
-// a chain takes some 35 ns per entry, a lane 500.  Large graphs have a hub whose
-// chain is longer than any lane row, and more chains beside it slow it (R-MAT-21
-// weighted k = 4, ms per solve at S = 768 / 2048 / 4096: 21.4 / 20.3 / 20.3,
-// R-MAT-20 weighted k = 8: 13.4 / 13.0 / 16.3); on small ones the lane rows are
-// what lasts (R-MAT-17: 3.6 / 4.6 / 10.2).  tune.py picks S per graph.
+// a chain takes some 35 ns per entry, a lane 200 to 500.  Large graphs have a hub
+// whose chain is longer than any lane row, and more chains beside it slow it
+// (R-MAT-21 weighted k = 4, ms per solve at S = 768 / 2048 / 4096: 21.4 / 20.3 /
+// 20.3, R-MAT-20 weighted k = 8: 13.4 / 13.0 / 16.3); on small ones the lane
+// rows are what lasts and wavefronts are to spare, the more the smaller the
+// graph.  Weighted R-MAT, k = 8, at S = 64 / 128 / 256 / 768: scale 10 (15,000
+// entries) 0.48 / 0.66 / 1.02 / 1.53, scale 12 (0.1 M) 0.91 / 0.96 / 1.01 / 3.60,
+// scale 14 (0.43 M) 2.12 / 2.09 / 2.11 / 4.69, scale 16 (1.8 M) 4.67 / 4.55 / 4.47
+// / 5.61, scale 17 (3.7 M) 3.63 / 3.58 / 3.57 / 3.43; the other slot counts and
+// rules order the same way.  tune.py picks S per graph.
 int default_lane_max(bool async_mode, int64_t nnz) {
   if (async_mode) return 1024;
+  if (nnz < (int64_t)1 << 18) return 64;
+  if (nnz < (int64_t)1 << 20) return 128;
+  if (nnz < (int64_t)1 << 21) return 256;
   return nnz < (int64_t)1 << 24 ? 768 : 2048;
 }
 
