@@ -481,7 +481,7 @@ struct lpa_batch {
   hipStream_t cap_stream = nullptr;  // private stream the iterations are captured on
   hipGraph_t graph = nullptr;
   hipGraphExec_t graph_exec = nullptr;
-  std::array<long long, 11> graph_key{};
+  std::array<long long, 12> graph_key{};
   bool async_mode = false;
   hipStream_t stream = nullptr;
   int device = 0;
@@ -508,6 +508,7 @@ struct lpa_batch {
   std::vector<lpa_handle *> loaded;
   int total_items = 0, total_hubs = 0, total_merge = 0, total_segs = 0, unfinished = 0;
   int det_hubs = 0;   // det mode: hubs of the loaded unfinished graphs
+  int max_items = 0;  // work items of the largest loaded unfinished graph
   bool unit = false;  // no loaded unfinished graph has weights
   bool poisoned = false;
   std::string err;
@@ -916,6 +917,7 @@ int batch_load(lpa_batch *b, lpa_handle *const *hs, int count) {
   int unfinished = 0;
   int64_t det_hubs = 0;
   bool wide = false, unit = true;
+  int max_items = 0;
   for (int g = 0; g < count; ++g) {
     lpa_handle *h = hs[g];
     if (!h) return LPA_ERR_ARG;
@@ -934,6 +936,7 @@ int batch_load(lpa_batch *b, lpa_handle *const *hs, int count) {
     unfinished += live ? 1 : 0;
     det_hubs += live && !b->async_mode ? h->desc.n_hubs : 0;
     unit = unit && (!live || h->w == nullptr);
+    if (live && move_items(h) > max_items) max_items = move_items(h);
     const int64_t next[4] = {
         (int64_t)pi[g] + (live ? move_items(h) : 0),
         (int64_t)ph[g] + (live && b->async_mode ? h->desc.n_hubs : 0),
@@ -952,6 +955,7 @@ int batch_load(lpa_batch *b, lpa_handle *const *hs, int count) {
   b->total_merge = pm[count];
   b->total_segs = ps[count];
   b->unfinished = unfinished;
+  b->max_items = max_items;
   b->det_hubs = (int)det_hubs;  // each is a work item: no more than total_items
   b->wide = wide;
   b->unit = unit;
@@ -1011,6 +1015,21 @@ int batch_read_status(lpa_batch *b) {
   return LPA_OK;
 }
 
+// One launch for all iterations, a workgroup per graph (k_solve), rather than one
+// per iteration over all graphs: where no wavefront has more than one work item,
+// one compute unit takes no longer over an iteration than a launch and the loads
+// behind it (unit-weight planted partitions, k = 8, us per solve with a launch
+// per iteration / in one: 200 vertices 191 / 118, 1,009 291 / 233, but 2,000 297 /
+// 343 and 4,000 309 / 527; 40 x 40 grid 219 / 135; weighted, 1,009: 344 / 302).  With
+// a graph for every compute unit the two are alike, so batches of more than a
+// quarter as many keep a launch per iteration.  Per-iteration events and a cap on
+// resident workgroups need one too.
+bool solve_in_one(const lpa_batch *b, const Launch &L) {
+  return !b->async_mode && !b->rescan && !b->shared_vars && b->k >= 1 && b->k <= 16 && !b->wide &&
+         L.det_hubs == 0 && b->blocks_cap == 0 && b->max_items <= kSolveBlock / kWave &&
+         L.G <= b->cus / 4;
+}
+
 // Run up to `iters` iterations of the loaded graphs; poll every check_every.
 // prof: handle whose per-iteration events are recorded (single-graph runs).
 int batch_iterate(lpa_batch *b, int iters, lpa_handle *prof) {
@@ -1031,13 +1050,14 @@ int batch_iterate(lpa_batch *b, int iters, lpa_handle *prof) {
   if (mg > b->cus * 4) mg = b->cus * 4;
   if (mg < 1) mg = 1;
   const bool profiling = prof && !prof->ev_beg.empty();
+  const bool small = !profiling && iters > 1 && solve_in_one(b, L);
   if (b->capture && b->check_every == 0 && !profiling) {
     // every remaining iteration as one hipGraph, captured on a private
     // stream once per launch shape and replayed on the caller's stream
     // (the descriptor table it reads is uploaded before each replay)
-    const std::array<long long, 11> key = {
+    const std::array<long long, 12> key = {
         iters,         grid,         mg,      L.G,            L.total_items, L.total_hubs,
-        L.total_merge, L.total_segs, b->wide, L.det_hubs > 0, b->unit};
+        L.total_merge, L.total_segs, b->wide, L.det_hubs > 0, b->unit,       small};
     if (!b->graph_exec || key != b->graph_key) {
       if (b->graph_exec) (void)hipGraphExecDestroy(b->graph_exec);
       if (b->graph) (void)hipGraphDestroy(b->graph);
@@ -1046,7 +1066,8 @@ int batch_iterate(lpa_batch *b, int iters, lpa_handle *prof) {
       HIP_TRY_B(b, hipStreamBeginCapture(b->cap_stream, hipStreamCaptureModeThreadLocal));
       hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, b->cap_stream, b->d_finished, 1);
       hipError_t e = hipSuccess;
-      for (int i = 0; i < iters && e == hipSuccess; ++i)
+      if (small) e = launch_solve(b->k, L, iters, b->cap_stream);
+      for (int i = 0; !small && i < iters && e == hipSuccess; ++i)
         e = launch_iteration(b->k, b->async_mode, b->rescan, b->hub_shared, b->shared_vars,
                              b->wide, L, grid, mg, b->cap_stream, nullptr, nullptr);
       hipGraph_t g = nullptr;
@@ -1062,6 +1083,10 @@ int batch_iterate(lpa_batch *b, int iters, lpa_handle *prof) {
     }
     HIP_TRY_B(b, hipGraphLaunch(b->graph_exec, b->stream));
     return LPA_OK;
+  }
+  if (small) {
+    const hipError_t e = launch_solve(b->k, L, iters, b->stream);
+    return e == hipSuccess ? LPA_OK : fail_hip_b(b, e, "solve launch");
   }
   for (int i = 0; i < iters; ++i) {  // the finished counter starts at 0 (batch_load)
     hipEvent_t eb = nullptr, ee = nullptr;

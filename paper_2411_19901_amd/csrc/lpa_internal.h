@@ -10,6 +10,7 @@ namespace lpa {
 
 constexpr int kWave = 64;
 constexpr int kBlock = 256;  // threads per workgroup for the move kernels
+constexpr int kSolveBlock = 1024;  // and for the solves of small graphs in one launch (k_solve)
 // Hub merge kernels: kHubLanes lanes per hub, kMergeHubs hubs per wavefront.
 constexpr int kHubLanes = 4;
 constexpr int kMergeHubs = kWave / kHubLanes;
@@ -223,6 +224,10 @@ int move_blocks_per_cu(int k, bool async_mode, bool rescan, bool shared_vars, bo
 // graph runs launch_iteration once per range with Launch::no_finish set,
 // then this once.
 hipError_t launch_finish(const Launch &L, hipStream_t s);
+// Up to `iters` iterations of every graph of the launch, one workgroup per graph
+// (k_solve: det mode, sketch rule with k <= 16, single scan, no hubs, 32-bit
+// positions).
+hipError_t launch_solve(int k, const Launch &L, int iters, hipStream_t s);
 
 // Modularity of one labelling (Eq. 1): vertices order[0, n_hubs) are read
 // by one wavefront per segment (or per hub without segments),

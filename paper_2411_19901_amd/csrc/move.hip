@@ -1583,6 +1583,45 @@ __device__ __forceinline__ void finish_last(const Launch &L) {
   if (threadIdx.x == 0) *L.ticket = 0;  // for the next launch
 }
 
+// Work item `local` of one graph: a hub, or 64 lane units, or 64 short units.
+template <int K, bool ASYNC, bool RS, class Pos, bool HUBS, bool UNIT, bool SV>
+__device__ __forceinline__ void move_item(const MoveArgs &a, Stage<kStageT, Pos, UNIT> &stage,
+                                          int local, int lane, unsigned long long &scanned_lane,
+                                          unsigned long long &scanned_w,
+                                          unsigned long long &changed_w) {
+  // det mode: one wavefront per hub first; async mode has none (its hubs
+  // are cut into segments, which are lane units), and neither have det
+  // launches over graphs without hubs, so their kernels carry no hub-chain
+  // code
+  int hub_items = 0;
+  if constexpr (!ASYNC && HUBS) {
+    hub_items = a.n_hubs;
+    if (local < hub_items) {
+      if constexpr (K == 0)
+        hub_vertex_det_bm<Pos>(a, stage.lab, local, scanned_w, changed_w);
+      else if constexpr (SV)
+        hub_vertex_det_sv<K, Pos>(a, local, scanned_w, changed_w);
+      else
+        hub_vertex_det<K, RS, Pos>(a, stage.lab, local, scanned_w, changed_w);
+      return;
+    }
+  }
+  // lane units (hub segments first in async mode, then whole vertices),
+  // then the short units
+  const int lane_local = local - hub_items;
+  const int units = a.n_seg + a.n_lane - a.n_short;
+  const int unit_items = (units + kWave - 1) / kWave;
+  if constexpr (!RS) {
+    if (lane_local >= unit_items) {
+      short_units<K, ASYNC, Pos>(a, (lane_local - unit_items) * (kWave * kShortRows),
+                                 scanned_lane, changed_w);
+      return;
+    }
+  }
+  lane_units<K, ASYNC, RS, Pos, SV, UNIT>(a, stage, lane_local * kWave + lane, scanned_lane,
+                                          changed_w);
+}
+
 // HUBS: the launch has hubs that take one wavefront each (det mode).  UNIT: no
 // graph of the launch has weights.
 template <int K, bool ASYNC, bool RS, class Pos, bool HUBS, bool UNIT, bool SV = false>
@@ -1609,38 +1648,9 @@ __device__ __forceinline__ void move_body(const Launch &L) {
     }
     MoveArgs a = make_args(d, iter);
     if constexpr (UNIT) a.w = nullptr;
-    const int local = item - as_const(L.prefix_items)[g];
-    // det mode: one wavefront per hub first; async mode has none (its hubs
-    // are cut into segments, which are lane units), and neither have det
-    // launches over graphs without hubs, so their kernels carry no hub-chain
-    // code
-    int hub_items = 0;
-    if constexpr (!ASYNC && HUBS) {
-      hub_items = a.n_hubs;
-      if (local < hub_items) {
-        if constexpr (K == 0)
-          hub_vertex_det_bm<Pos>(a, stage[wib].lab, local, scanned_w, changed_w);
-        else if constexpr (SV)
-          hub_vertex_det_sv<K, Pos>(a, local, scanned_w, changed_w);
-        else
-          hub_vertex_det<K, RS, Pos>(a, stage[wib].lab, local, scanned_w, changed_w);
-        continue;
-      }
-    }
-    // lane units (hub segments first in async mode, then whole vertices),
-    // then the short units
-    const int lane_local = local - hub_items;
-    const int units = a.n_seg + a.n_lane - a.n_short;
-    const int unit_items = (units + kWave - 1) / kWave;
-    if constexpr (!RS) {
-      if (lane_local >= unit_items) {
-        short_units<K, ASYNC, Pos>(a, (lane_local - unit_items) * (kWave * kShortRows),
-                                   scanned_lane, changed_w);
-        continue;
-      }
-    }
-    lane_units<K, ASYNC, RS, Pos, SV, UNIT>(
-        a, stage[wib], lane_local * kWave + lane, scanned_lane, changed_w);
+    move_item<K, ASYNC, RS, Pos, HUBS, UNIT, SV>(
+        a, stage[wib], item - as_const(L.prefix_items)[g], lane, scanned_lane, scanned_w,
+        changed_w);
   }
   flush_last_counts(cdN, csc, scanned_lane, scanned_w, changed_w, wib);
   if (L.fuse_finish) finish_last(L);
@@ -2303,6 +2313,91 @@ __global__ __launch_bounds__(256) void k_hub_shared(Launch L) {
 __global__ void k_finish(Launch L) {
   for (int g = blockIdx.x * blockDim.x + threadIdx.x; g < L.G; g += gridDim.x * blockDim.x)
     finish_graph(L, g);
+}
+
+// All remaining iterations of small graphs in one launch, one workgroup per
+// graph (det mode, single scan, no hubs, 32-bit positions; the host's solve_in_one
+// says which).  A small graph's iteration is one chain of dependent loads and,
+// as a launch of its own, its start and its stop test's atomics; here the arrays
+// stay in the compute unit's cache, a barrier parts the iterations and the counts
+// are summed in LDS.  What is left is the sketch updates of four wavefronts on
+// each SIMD: 11 us per iteration of 16 items (1,009 vertices, unit weights, k = 8:
+// 291 to 233 us per solve; 200 vertices: 191 to 118).  Every wavefront of a workgroup is
+// on one compute unit and reads and writes through its one vector cache, so a
+// barrier (which waits for the stores) is all the ordering that the next
+// iteration's reads need; what scalar loads read (descriptors) is not written.
+template <int K, bool UNIT>
+__global__ __launch_bounds__(kSolveBlock) void k_solve(Launch L, int iters) {
+  constexpr int NW = kSolveBlock / kWave;
+  __shared__ Stage<kStageT, int, UNIT> stage[NW];
+  __shared__ unsigned long long s_changed[2][NW], s_scanned[2][NW];
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wib = rfl(threadIdx.x / kWave);
+  for (int g = blockIdx.x; g < L.G; g += gridDim.x) {
+    DescRef d = desc_of(L, g);
+    GraphStatus *st = d.st;
+    const int first = rfl(st->iter), was_done = rfl(st->done);
+    __syncthreads();  // read by all, before thread 0 writes it
+    int iter = first, done = was_done, changed = 0;
+    for (int i = 0; i < iters && !done; ++i) {
+      unsigned long long scanned_lane = 0, changed_w = 0, scanned_w = 0;
+      MoveArgs a = make_args(d, iter);
+      if constexpr (UNIT) a.w = nullptr;
+      for (int item = wib; item < d.items; item += NW)
+        move_item<K, false, false, int, false, UNIT, false>(a, stage[wib], item, lane,
+                                                            scanned_lane, scanned_w, changed_w);
+#pragma unroll
+      for (int off = kWave / 2; off >= 1; off >>= 1) scanned_lane += __shfl_xor(scanned_lane, off);
+      // two sets of sums, used in turn: one barrier per iteration
+      if (lane == 0) {
+        s_changed[i & 1][wib] = changed_w;
+        s_scanned[i & 1][wib] = scanned_lane + scanned_w;
+      }
+      __syncthreads();
+      unsigned long long c = 0, t = 0;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        c += s_changed[i & 1][w];
+        t += s_scanned[i & 1][w];
+      }
+      changed = rfl((int)c);  // at most n < 2^31
+      if (threadIdx.x == 0) {
+        d.dN[iter] = c;
+        d.scanned[iter] = t;
+      }
+      // the stop test of finish_graph
+      const bool pl = d.rho > 0 && iter % d.rho == 0;
+      const double frac = (double)changed / (double)d.n;
+      ++iter;
+      done = rfl((!pl && frac < d.tol) || iter >= d.max_iter ? 1 : 0);
+    }
+    if (threadIdx.x == 0) {
+      st->iter = iter;
+      st->done = done;
+      if (done && !was_done) atomicAdd(L.finished, 1);
+      L.status_out[3 * g] = iter;
+      L.status_out[3 * g + 1] = done;
+      L.status_out[3 * g + 2] = changed;
+    }
+  }
+}
+
+template <bool UNIT>
+static hipError_t launch_solve_u(int k, const Launch &L, int iters, hipStream_t s) {
+  const dim3 grid(L.G), block(kSolveBlock);
+  switch (k) {
+    case 1: hipLaunchKernelGGL((k_solve<1, UNIT>), grid, block, 0, s, L, iters); break;
+    case 2: hipLaunchKernelGGL((k_solve<2, UNIT>), grid, block, 0, s, L, iters); break;
+    case 4: hipLaunchKernelGGL((k_solve<4, UNIT>), grid, block, 0, s, L, iters); break;
+    case 8: hipLaunchKernelGGL((k_solve<8, UNIT>), grid, block, 0, s, L, iters); break;
+    case 16: hipLaunchKernelGGL((k_solve<16, false>), grid, block, 0, s, L, iters); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_solve(int k, const Launch &L, int iters, hipStream_t s) {
+  return L.unit ? launch_solve_u<true>(k, L, iters, s) : launch_solve_u<false>(k, L, iters, s);
 }
 
 // The single-scan move kernel of a launch (see move_body): its instances leave
