@@ -1,5 +1,5 @@
 """Det solves of small graphs in one launch, one workgroup of 16 wavefronts per
-graph: at most 16 work items of 64 (or, for the rows of at most 4 entries, 128)
+graph: at most 17 work items of 64 (or, for the rows of at most 4 entries, 128)
 vertices.  Graphs on both sides of that limit, alone, in a batch, captured, in
 single steps and resumed from a saved state give the oracle's labels, iteration
 count and per-iteration counts bit for bit."""
@@ -26,7 +26,7 @@ def sbm(n, weights, seed=3):
     return inputs.with_uniform_weights(g, seed) if weights else g
 
 
-@pytest.mark.parametrize("n", [2, 63, 64, 65, 1000, 1023, 1024, 1025, 1100])
+@pytest.mark.parametrize("n", [2, 63, 64, 65, 1000, 1023, 1024, 1025, 1100, 1300])
 @pytest.mark.parametrize("weights", [False, True])
 @pytest.mark.parametrize("k", [1, 2, 4, 8, 16])
 def test_det_parity(n, weights, k):
