@@ -60,6 +60,24 @@ __host__ __device__ inline int degree_class(int d, int lane_max) {
   return kHubClasses + kLaneBuckets + (kLaneExact - d);
 }
 
+// CSR positions that the staging of unit-weight rows reads (stage_cols in
+// move.hip), which loads every slot of a step: slot `at` of a row of len entries
+// at beg reads entry `at` or, past the row's end, the last one.  A row without
+// entries reads one of another row of its wavefront: its own position means
+// nothing (it is 0 for an inactive vertex, and entry 0 of a range of a streamed
+// graph lies before the range's buffer).
+template <class Pos>
+__host__ __device__ __forceinline__ Pos staged_position(Pos beg, int len, int at) {
+  const int last = len > 1 ? len - 1 : 0;
+  return beg + (Pos)(at < last ? at : last);
+}
+// Position to stage a row with; other: that of a row of the wavefront that has
+// entries (some row has).
+template <class Pos>
+__host__ __device__ __forceinline__ Pos staged_begin(Pos beg, int len, Pos other) {
+  return len > 0 ? beg : other;
+}
+
 // Device pointers into device or mapped host memory, never LDS or scratch.
 // Typed as the global address space so that the compiler emits global
 // (not flat) loads and stores: flat accesses may alias LDS, which forbids

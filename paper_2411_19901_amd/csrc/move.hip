@@ -240,7 +240,8 @@ __device__ __forceinline__ void stage_load(const MoveArgs &a, Stage<T, Pos, fals
 // UNIT: the columns of a step go into registers, all of a lane's slots in
 // flight together, the next step's while this one is consumed; then the
 // labels, eight slots at a time.  A slot past its row's end reads the row's last
-// entry and the label of vertex 0, lines that others of the step read too, so
+// entry (without any, another row's: staged_position) and the label of vertex
+// 0, lines that others of the step read too, so
 // no branch stands between a step's loads: it waits for memory twice, or three
 // times for 16 entries, instead of eight times in stage_load.  Such graphs have
 // no weights to stream and rows of a few labels that hit the caches, so they
@@ -257,8 +258,8 @@ __device__ __forceinline__ void stage_cols(const MoveArgs &a, const Stage<T, Pos
 #pragma unroll
   for (int i = 0; i < TW; ++i) {
     const int slot = i * kWave + lane, r = slot / TW, j = slot % TW;
-    const int e = min(t0 + j, max(st.row[r].x, 1) - 1);
-    c[i] = __builtin_nontemporal_load(element(a.col, st.beg[r] + (Pos)e));
+    c[i] = __builtin_nontemporal_load(
+        element(a.col, staged_position<Pos>(st.beg[r], st.row[r].x, t0 + j)));
   }
 }
 
@@ -302,10 +303,12 @@ template <bool KEEP, int T, class Pos, bool UNIT, class Feed>
 __device__ __forceinline__ int staged_rows(const MoveArgs &a, Stage<T, Pos, UNIT> &st, int lane,
                                            Pos beg, int len, int self, Feed &&feed) {
   static_assert(T == 16, "step widths 4, 8 and 16");
-  st.beg[lane] = beg;
+  if constexpr (!UNIT) st.beg[lane] = beg;
   st.row[lane] = make_int2(len, self);
   const int maxlen = wave_max(len);
   if (maxlen == 0) return 0;
+  if constexpr (UNIT)
+    st.beg[lane] = staged_begin(beg, len, rl_as(beg, __ffsll((long long)__ballot(len > 0)) - 1));
   wave_lds_sync();
   int t0 = 0;
   // this lane's row: its first entries of a step of tw staged ones (later

@@ -31,6 +31,19 @@ __device__ __forceinline__ float rl_f(float x, int lane) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
 }
 
+// readlane of an int or a long long
+template <class T>
+__device__ __forceinline__ T rl_as(T x, int lane) {
+  if constexpr (sizeof(T) == 8) {
+    const unsigned long long u = (unsigned long long)x;
+    const unsigned lo = (unsigned)rl((int)(unsigned)u, lane);
+    const unsigned hi = (unsigned)rl((int)(unsigned)(u >> 32), lane);
+    return (T)(((unsigned long long)hi << 32) | lo);
+  } else {
+    return rl(x, lane);
+  }
+}
+
 // DPP move across lanes (CTRL: the dpp_ctrl encoding), every row and bank
 // enabled; the source lanes are always active where these are used.
 template <int CTRL>
