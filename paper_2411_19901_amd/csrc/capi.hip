@@ -498,7 +498,12 @@ struct lpa_batch {
   int32_t *d_finished = nullptr;
   uint32_t *d_ticket = nullptr;
   int32_t *d_status = nullptr;  // [3 * cap]: iter, done, dN of the last launched iteration
-  void *hblock = nullptr;  // pinned host mirror of the same layout
+  // Pinned host mirrors of the same layout, written in turn: an upload that is
+  // still queued keeps its source while the next call prepares its own
+  // (batch_load).  The h_* pointers lie in the one written last.
+  void *hblock[2] = {nullptr, nullptr};
+  int mirror = 0;
+  int uploads = 0;  // since the stream was last waited for
   GraphDesc *h_desc = nullptr;
   int32_t *h_prefix = nullptr;
   int32_t *h_finished = nullptr;
@@ -853,6 +858,15 @@ int state_in(lpa_handle *h, const void *in, void *st, size_t elem, bool in_is_ho
 }
 
 // --- batches -----------------------------------------------------------------
+void use_mirror(lpa_batch *b, int i) {
+  char *hh = (char *)b->hblock[i];
+  b->mirror = i;
+  b->h_desc = (GraphDesc *)hh;
+  b->h_prefix = (int32_t *)(hh + b->off_prefix);
+  b->h_finished = (int32_t *)(hh + b->off_finished);
+  b->h_status = (int32_t *)(hh + b->off_status);
+}
+
 int batch_alloc(lpa_batch *b) {
   const size_t cap = (size_t)b->capacity;
   size_t off = 0;
@@ -868,21 +882,18 @@ int batch_alloc(lpa_batch *b) {
     (void)hipGetLastError();
     return LPA_ERR_NOMEM;
   }
-  if (hipHostMalloc(&b->hblock, off, hipHostMallocDefault) != hipSuccess) {
-    (void)hipGetLastError();
-    return LPA_ERR_NOMEM;
-  }
-  char *d = (char *)b->dblock, *hh = (char *)b->hblock;
+  for (void *&hb : b->hblock)
+    if (hipHostMalloc(&hb, off, hipHostMallocDefault) != hipSuccess) {
+      (void)hipGetLastError();
+      return LPA_ERR_NOMEM;
+    }
+  char *d = (char *)b->dblock;
   b->d_desc = (GraphDesc *)d;
-  b->h_desc = (GraphDesc *)hh;
   b->d_prefix = (int32_t *)(d + b->off_prefix);
-  b->h_prefix = (int32_t *)(hh + b->off_prefix);
   b->d_finished = (int32_t *)(d + b->off_finished);
-  b->h_finished = (int32_t *)(hh + b->off_finished);
   b->d_status = (int32_t *)(d + b->off_status);
   b->d_ticket = (uint32_t *)(b->d_finished + 1);
-  memset(hh + b->off_finished, 0, b->off_status - b->off_finished);
-  b->h_status = (int32_t *)(hh + b->off_status);
+  use_mirror(b, 0);
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return LPA_ERR_HIP;
   b->device = dev;
@@ -902,7 +913,8 @@ void batch_release(lpa_batch *b) {
   if (b->graph) (void)hipGraphDestroy(b->graph);
   if (b->cap_stream) (void)hipStreamDestroy(b->cap_stream);
   if (b->dblock) (void)hipFree(b->dblock);
-  if (b->hblock) (void)hipHostFree(b->hblock);
+  for (void *hb : b->hblock)
+    if (hb) (void)hipHostFree(hb);
   delete b;
 }
 
@@ -911,6 +923,13 @@ int move_items(const lpa_handle *h) { return h->desc.items; }
 // Upload the descriptor table for hs[0..count).
 int batch_load(lpa_batch *b, lpa_handle *const *hs, int count) {
   if (count < 0 || count > b->capacity) return LPA_ERR_ARG;
+  // write the mirror that the last upload did not read; with both read since
+  // the stream was last waited for (resets in a row), wait for it
+  if (b->uploads >= 2) {
+    HIP_TRY_B(b, hipStreamSynchronize(b->stream));
+    b->uploads = 0;
+  }
+  use_mirror(b, b->mirror ^ 1);
   int32_t *pi = b->h_prefix, *ph = b->h_prefix + (b->capacity + 1),
           *pm = b->h_prefix + 2 * (b->capacity + 1), *ps = b->h_prefix + 3 * (b->capacity + 1);
   pi[0] = ph[0] = pm[0] = ps[0] = 0;
@@ -963,10 +982,11 @@ int batch_load(lpa_batch *b, lpa_handle *const *hs, int count) {
   // descriptors, prefix sums, finished counter (0) and ticket (0) lie in one
   // piece: one copy where the unused descriptors between them are few
   constexpr size_t kOneCopy = 64 << 10;
+  ++b->uploads;
   const size_t desc_bytes = (size_t)count * sizeof(GraphDesc);
   memset(b->h_finished, 0, b->off_status - b->off_finished);
   if (b->off_prefix - desc_bytes <= kOneCopy) {
-    HIP_TRY_B(b, hipMemcpyAsync(b->dblock, b->hblock, b->off_status, hipMemcpyHostToDevice,
+    HIP_TRY_B(b, hipMemcpyAsync(b->dblock, b->h_desc, b->off_status, hipMemcpyHostToDevice,
                                 b->stream));
   } else {
     HIP_TRY_B(b, hipMemcpyAsync(b->d_desc, b->h_desc, desc_bytes, hipMemcpyHostToDevice, b->stream));
@@ -1006,6 +1026,7 @@ int batch_read_status(lpa_batch *b) {
                               b->off_status - b->off_finished + 3 * (size_t)G * sizeof(int32_t),
                               hipMemcpyDeviceToHost, b->stream));
   HIP_TRY_B(b, hipStreamSynchronize(b->stream));
+  b->uploads = 0;
   for (int g = 0; g < G; ++g) {
     lpa_handle *h = b->loaded[g];
     if (h->finished) continue;
