@@ -715,12 +715,45 @@ int check_ready(lpa_handle *h) {
 // scale 14 (0.43 M) 2.12 / 2.09 / 2.11 / 4.69, scale 16 (1.8 M) 4.67 / 4.55 / 4.47
 // / 5.61, scale 17 (3.7 M) 3.63 / 3.58 / 3.57 / 3.43; the other slot counts and
 // rules order the same way.  tune.py picks S per graph.
+struct DetStep {
+  int64_t below;  // entries
+  int lane_max;
+};
+constexpr DetStep kDetSteps[] = {{(int64_t)1 << 18, 64},
+                                 {(int64_t)1 << 20, 128},
+                                 {(int64_t)1 << 21, 256},
+                                 {(int64_t)1 << 24, 768},
+                                 {INT64_MAX, 2048}};
+
 int default_lane_max(bool async_mode, int64_t nnz) {
   if (async_mode) return 1024;
-  if (nnz < (int64_t)1 << 18) return 64;
-  if (nnz < (int64_t)1 << 20) return 128;
-  if (nnz < (int64_t)1 << 21) return 256;
-  return nnz < (int64_t)1 << 24 ? 768 : 2048;
+  for (const DetStep &s : kDetSteps)
+    if (nnz < s.below) return s.lane_max;
+  return kDetSteps[4].lane_max;
+}
+
+// Most hubs and hub segments of a graph of nnz entries: hubs have more than S
+// entries each; a hub of degree d > S has ceil(d / S) < 2 d / S segments.
+struct HubBounds {
+  int64_t hubs, segs;
+};
+HubBounds hub_bounds(int64_t nnz, int lane_max) {
+  return {nnz / (lane_max + 1) + 1, 2 * (nnz / lane_max) + 2};
+}
+
+// Tables for the hubs of a graph of nnz entries.  With the default threshold of
+// det mode, which grows with nnz, also for those of every smaller graph: what is
+// reserved never shrinks as nnz grows, so a workspace sized for a caller's
+// largest graph holds the smaller ones.
+HubBounds hub_tables(int64_t nnz, int lane_max, bool det_default) {
+  HubBounds b = hub_bounds(nnz, lane_max);
+  if (det_default)
+    for (const DetStep &s : kDetSteps) {
+      if (nnz < s.below) break;
+      const HubBounds t = hub_bounds(s.below - 1, s.lane_max);
+      b = {std::max(b.hubs, t.hubs), std::max(b.segs, t.segs)};
+    }
+  return b;
 }
 
 // labels after the iterations run so far
@@ -737,9 +770,9 @@ struct Layout {
 
 size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// bound_partials: reserve the partial sketches for the largest possible
-// number of hub segments (a caller workspace); otherwise lpa_init sizes them
-// once the segments are planned.
+// lane_max: the caller's threshold, 0 for the default.  bound_partials: reserve
+// the partial sketches for the largest possible number of hub segments (a caller
+// workspace); otherwise lpa_init sizes them once the segments are planned.
 Layout plan_layout(int32_t n, int64_t nnz, int k, int max_iter, bool async_mode, int lane_max,
                    bool rescan, bool bound_partials, bool ranked) {
   Layout L{};
@@ -770,11 +803,10 @@ Layout plan_layout(int32_t n, int64_t nnz, int k, int max_iter, bool async_mode,
     L.colr = take((size_t)nnz * 4);
     L.tmp = take((size_t)n * 4);
   }
-  // hubs have more than S entries each; a hub of degree d > S has
-  // ceil(d / S) < 2 d / S segments.  Async mode scans the segments as work
-  // items; both modes spread modularity's reads of a hub over them.
-  const int64_t hubs = nnz / (lane_max + 1) + 1;
-  const int64_t segs = 2 * (nnz / lane_max) + 2;
+  // async mode scans the hub segments as work items; both modes spread
+  // modularity's reads of a hub over them
+  const int S = lane_max > 0 ? lane_max : default_lane_max(async_mode, nnz);
+  const auto [hubs, segs] = hub_tables(nnz, S, !async_mode && lane_max <= 0);
   if (segs >= kMaxSegs) {  // work items of one iteration must fit int32
     if (async_mode) {
       L.too_many_segs = true;
@@ -1214,8 +1246,7 @@ int lpa_workspace_bytes(int32_t n, int64_t nnz, int k, int max_iter, const lpa_c
   if (rc) return rc;
   if ((rc = check_k(k, cfg.flags)) != LPA_OK) return rc;
   const bool async_mode = (cfg.flags & LPA_MODE_MASK) == LPA_MODE_ASYNC;
-  const int lane_max = cfg.lane_max_degree > 0 ? cfg.lane_max_degree : default_lane_max(async_mode, nnz);
-  const Layout Ly = plan_layout(n, nnz, k, max_iter, async_mode, lane_max,
+  const Layout Ly = plan_layout(n, nnz, k, max_iter, async_mode, cfg.lane_max_degree,
                                 (cfg.flags & LPA_RESCAN) != 0, true,
                                 (cfg.flags & LPA_RANKED_LAYOUT) != 0);
   if (Ly.too_many_segs) return LPA_ERR_UNSUPPORTED;
@@ -1613,7 +1644,7 @@ int lpa_init(const lpa_graph *g, const float *weights, int k, double tol, int ma
   const int n = h->n;
   const bool bound_partials = cfg.workspace != nullptr;
   const bool ranked = (cfg.flags & LPA_RANKED_LAYOUT) != 0;
-  const Layout Ly = plan_layout(n, h->nnz, k, max_iter, h->async_mode, h->lane_max,
+  const Layout Ly = plan_layout(n, h->nnz, k, max_iter, h->async_mode, cfg.lane_max_degree,
                                 (cfg.flags & LPA_RESCAN) != 0, bound_partials, ranked);
   if (Ly.too_many_segs) return bail(set_err(h, LPA_ERR_UNSUPPORTED, "too many hub segments"));
   if (cfg.workspace) {
