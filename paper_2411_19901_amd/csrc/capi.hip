@@ -21,12 +21,15 @@ using namespace lpa;
 // ===========================================================================
 namespace {
 
+// The kernels below walk vertices and counts with unsigned numbers: the last step
+// past n < 2^31 - 1, a grid or a block's ids further, does not fit int.
 constexpr int kAuxBlock = 256;
 constexpr int kPrefixArrays = 4;  // per-graph prefix sums kept for a batched launch
 
 // pos[order[p]] = p: the degree-order position of every vertex.
 __global__ void k_positions(const int32_t *order, int n, int32_t *pos) {
-  for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < n; p += gridDim.x * blockDim.x)
+  for (unsigned p = blockIdx.x * blockDim.x + threadIdx.x; p < (unsigned)n;
+       p += gridDim.x * blockDim.x)
     pos[order[p]] = p;
 }
 
@@ -41,12 +44,14 @@ __global__ void k_remap_cols(const int32_t *col, int64_t nnz, const int32_t *pos
 // out[order[p]] = st[p] and st[p] = in[order[p]].
 template <class T>
 __global__ void k_unrank(const int32_t *order, const T *st, int n, T *out) {
-  for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < n; p += gridDim.x * blockDim.x)
+  for (unsigned p = blockIdx.x * blockDim.x + threadIdx.x; p < (unsigned)n;
+       p += gridDim.x * blockDim.x)
     out[order[p]] = st[p];
 }
 template <class T>
 __global__ void k_rank(const int32_t *order, const T *in, int n, T *st) {
-  for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < n; p += gridDim.x * blockDim.x)
+  for (unsigned p = blockIdx.x * blockDim.x + threadIdx.x; p < (unsigned)n;
+       p += gridDim.x * blockDim.x)
     st[p] = in[order[p]];
 }
 
@@ -57,7 +62,8 @@ __global__ void k_fill_u8(uint8_t *p, size_t count, uint8_t v) {
 }
 
 __global__ void k_normalize_u8(uint8_t *p, int n) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
+  for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < (unsigned)n;
+       i += gridDim.x * blockDim.x)
     p[i] = p[i] ? 1 : 0;
 }
 
@@ -85,7 +91,8 @@ __global__ void k_validate(int n, int64_t nnz, RowPtr rp, const int32_t *col, co
 
 __global__ void k_check_labels(const int32_t *lab, int n, int *bad) {
   int b = 0;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+  for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < (unsigned)n;
+       i += gridDim.x * blockDim.x) {
     const int c = lab[i];
     if (c < 0 || c >= n) b = 8;
   }
@@ -109,18 +116,14 @@ constexpr int64_t kMaxEntries = (int64_t)1 << 62;
 constexpr int64_t kMaxSegs = (int64_t)1 << 30;
 constexpr int kScanChunk = 4096;  // entries per block of the prefix sum
 
-// Ids per block: a small graph is cut finer, so that its binning takes few
-// steps; a large one coarser, so that the count matrix stays small.
-int bin_ids(int n) { return n <= 1 << 18 ? 512 : n <= 1 << 21 ? 2048 : 4096; }
-
 __global__ void k_bin_count(int v0, int n, RowPtr rp, int lane_max, int ids, int nblk,
                             unsigned *counts) {
   __shared__ unsigned cnt[kBinClasses];
   for (int c = threadIdx.x; c < kBinClasses; c += blockDim.x) cnt[c] = 0;
   __syncthreads();
-  const int b0 = blockIdx.x * ids;
-  for (int u = b0 + threadIdx.x; u < b0 + ids && u < n; u += blockDim.x) {
-    const int v = v0 + u;
+  const unsigned b0 = blockIdx.x * (unsigned)ids;
+  for (unsigned u = b0 + threadIdx.x; u < b0 + ids && u < (unsigned)n; u += blockDim.x) {
+    const int v = v0 + (int)u;
     const int d = (int)(rp[v + 1] - rp[v]);
     atomicAdd(&cnt[degree_class(d, lane_max)], 1u);
   }
@@ -222,10 +225,11 @@ __global__ __launch_bounds__(256) void k_bin_place(int v0, int n, RowPtr rp, int
   for (int i = threadIdx.x; i < 4 * kBinClasses; i += blockDim.x) (&next[0][0])[i] = 0;
   __syncthreads();
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const int u0 = blockIdx.x * ids + wid * (ids / 4), u1 = min(n, u0 + ids / 4);
+  const unsigned u0 = blockIdx.x * (unsigned)ids + (unsigned)(wid * (ids / 4));
+  const unsigned u1 = min((unsigned)n, u0 + ids / 4);
   unsigned *mine = next[wid];
-  for (int u = u0 + lane; u < u1; u += 64) {
-    const int v = v0 + u;
+  for (unsigned u = u0 + lane; u < u1; u += 64) {
+    const int v = v0 + (int)u;
     atomicAdd(&mine[degree_class((int)(rp[v + 1] - rp[v]), lane_max)], 1u);
   }
   __syncthreads();
@@ -241,8 +245,9 @@ __global__ __launch_bounds__(256) void k_bin_place(int v0, int n, RowPtr rp, int
   }
   __syncthreads();
   const unsigned long long below = (1ull << lane) - 1ull;
-  for (int r = u0; r < u1; r += 64) {
-    const int u = r + lane, v = v0 + u;
+  for (unsigned r = u0; r < u1; r += 64) {
+    const unsigned u = r + lane;
+    const int v = v0 + (int)u;
     const bool on = u < u1;
     const int cls = on ? degree_class((int)(rp[v + 1] - rp[v]), lane_max) : 0;
     unsigned long long same = __ballot(on);
@@ -370,8 +375,8 @@ __device__ __forceinline__ void reset_graph(const GraphDesc &gd) {
     }
   }
   if (blockIdx.x == 0) {
-    const int i = 4 * n4 + (int)threadIdx.x;
-    if (i < gd.n) {
+    if ((int)threadIdx.x < gd.n - 4 * n4) {
+      const int i = 4 * n4 + (int)threadIdx.x;
       const int c = gd.ranked ? gd.order[i] : i;
       gd.C[0][i] = c;
       gd.act[0][i] = 1;
@@ -406,7 +411,8 @@ __global__ void k_status_clear_err(GraphStatus *st) {
 }
 
 __global__ void k_zero_i32(int32_t *p, int count) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < count; i += gridDim.x * blockDim.x)
+  for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < (unsigned)count;
+       i += gridDim.x * blockDim.x)
     p[i] = 0;
 }
 
@@ -425,7 +431,8 @@ constexpr int kModSqBlocks = 1024;
 __global__ __launch_bounds__(kAuxBlock) void k_mod_sq(double *tot, int n, double *acc) {
   __shared__ double part[kAuxBlock / 64];
   double s = 0.0;
-  for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < n; c += gridDim.x * blockDim.x) {
+  for (unsigned c = blockIdx.x * blockDim.x + threadIdx.x; c < (unsigned)n;
+       c += gridDim.x * blockDim.x) {
     const double x = tot[c];
     s += x * x;
     tot[c] = 0.0;
@@ -455,7 +462,8 @@ __global__ void k_scan_floor(const int32_t *col, const float *w, const int32_t *
 }
 
 __global__ void k_zero_d(double *p, int count) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < count; i += gridDim.x * blockDim.x)
+  for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < (unsigned)count;
+       i += gridDim.x * blockDim.x)
     p[i] = 0.0;
 }
 
@@ -786,7 +794,7 @@ Layout plan_layout(int32_t n, int64_t nnz, int k, int max_iter, bool async_mode,
   L.ncls = kBinClasses;
   // a streamed graph bins its id ranges too: no range of up to n ids has more
   // blocks than n itself or than 2^21 / 2048
-  const size_t ids = (size_t)bin_ids(n), nblk = ((size_t)n + ids - 1) / ids;
+  const size_t nblk = (size_t)bin_blocks(n);
   const size_t cells = (size_t)kBinClasses * std::max(nblk, std::min<size_t>((size_t)n / 512 + 1, 1024));
   const size_t chunks = (cells + kScanChunk - 1) / kScanChunk;
   L.st = take(sizeof(GraphStatus));
@@ -1266,7 +1274,7 @@ hipError_t bin_range(lpa_handle *h, int v0, int nr, int32_t *order, int *hubs, i
   if (shorts) *shorts = 0;
   if (mids) *mids = 0;
   if (nr <= 0) return hipSuccess;
-  const int ids = bin_ids(nr), nblk = (nr + ids - 1) / ids;
+  const int ids = bin_ids(nr), nblk = bin_blocks(nr);
   const size_t cells = (size_t)kBinClasses * nblk;
   const int nchunks = (int)((cells + kScanChunk - 1) / kScanChunk);
   unsigned *counts = (unsigned *)h->desc.C[0];
@@ -1455,9 +1463,9 @@ int stream_bin(lpa_handle *h) {
         HIP_TRY(h, hipGetLastError());
       }
       d.n_seg = nseg;
-      d.items = (nseg + lanes + kWave - 1) / kWave;
+      d.items = (int)lane_items((int64_t)nseg + lanes, 0);
     } else {
-      d.items = hubs + (lanes + kWave - 1) / kWave;
+      d.items = (int)(hubs + lane_items(lanes, 0));
     }
     S.items[p] = d.items;
     S.hubs[p] = hubs;

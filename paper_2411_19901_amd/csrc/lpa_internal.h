@@ -60,6 +60,15 @@ __host__ __device__ inline int degree_class(int d, int lane_max) {
   return kHubClasses + kLaneBuckets + (kLaneExact - d);
 }
 
+// Ids per block of the degree binning: a small graph is cut finer, so that its
+// binning takes few steps; a large one coarser, so that the count matrix stays
+// small.  And the blocks of n ids, for any n that fits int.
+__host__ inline int bin_ids(int n) { return n <= 1 << 18 ? 512 : n <= 1 << 21 ? 2048 : 4096; }
+__host__ inline int bin_blocks(int n) {
+  const int ids = bin_ids(n);
+  return n / ids + (n % ids != 0 ? 1 : 0);
+}
+
 // CSR positions that the staging of unit-weight rows reads (stage_cols in
 // move.hip), which loads every slot of a step: slot `at` of a row of len entries
 // at beg reads entry `at` or, past the row's end, the last one.  A row without

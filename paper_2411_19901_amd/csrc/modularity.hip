@@ -325,7 +325,7 @@ __global__ __launch_bounds__(kBlock) void k_modularity(ModArgs m) {
   const int mid_items = (m.n_mid + kMidRows - 1) / kMidRows;
   // staged lane rows, then the short ones
   const int first_row = m.n_hubs + m.n_mid, lane_rows = m.n_lane - m.n_mid - m.n_short;
-  const int row_items = (lane_rows + kWave - 1) / kWave;
+  const int row_items = (int)(((unsigned)lane_rows + kWave - 1) / kWave);
   const int items = hub_items + mid_items + (int)lane_items(m.n_lane - m.n_mid, m.n_short);
   double k_acc = 0.0, in_acc = 0.0;
   Held held = {-1, 0.0};

@@ -1613,7 +1613,7 @@ __device__ __forceinline__ void move_item(const MoveArgs &a, Stage<kStageT, Pos,
   // then the short units
   const int lane_local = local - hub_items;
   const int units = a.n_seg + a.n_lane - a.n_short;
-  const int unit_items = (units + kWave - 1) / kWave;
+  const int unit_items = (int)(((unsigned)units + kWave - 1) / kWave);
   if constexpr (!RS) {
     if (lane_local >= unit_items) {
       short_units<K, ASYNC, Pos>(a, (lane_local - unit_items) * (kWave * kShortRows),
