@@ -30,7 +30,9 @@ from typing import Dict, Iterable, List, Optional, Sequence, Tuple
 
 import numpy as np
 
-DEFAULT_CANDIDATES = (256, 512, 1024, 2048, 4096, 8192)
+# among them the library's own defaults for every size (see lane_max_degree in
+# include/lpa.h), so that tuning does not end with less than leaving S alone
+DEFAULT_CANDIDATES = (64, 128, 256, 512, 768, 1024, 2048, 4096, 8192)
 DEFAULT_BLOCKS = (0, 3, 2)
 
 
