@@ -194,7 +194,8 @@ struct Launch {
   int32_t *status_out;      // [3 * G]: iter, done, dN of the iteration just run (0: none)
   int32_t no_finish;        // 1: launch_iteration leaves out the stop test
   // 1: the move kernel runs the stop test itself, in the workgroup that ends
-  // last (set by launch_iteration where it is the iteration's only kernel)
+  // last (set by launch_iteration for small launches where it is the iteration's
+  // only kernel)
   int32_t fuse_finish;
   uint32_t *ticket;         // workgroups of that kernel that have ended; 0 between launches
 };

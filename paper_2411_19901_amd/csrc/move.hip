@@ -1569,8 +1569,10 @@ __device__ __forceinline__ void finish_graph(const Launch &L, int g) {
 // from the others are those atomics, so each workgroup waits for its own to
 // complete before it takes its ticket; a fence would write its XCD's L2 back,
 // once per workgroup (the 4096^2 grid's iterations: 0.39 against 0.34 ms).  A
-// launch of its own took 4 us and the gap before it.  Every thread of the
-// workgroup must call it, after its counts are flushed.
+// launch of its own takes 4 us and the gap before it, whatever the size; the
+// tickets are atomics on one address, one per workgroup, in launches after
+// convergence too.  So small launches run the test here (kFuseBlocks).  Every
+// thread of the workgroup must call it, after its counts are flushed.
 __device__ __forceinline__ void finish_last(const Launch &L) {
   __shared__ int last;
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -2415,6 +2417,17 @@ static auto move_kernel(bool hubs, bool unit) -> void (*)(Launch) {
   return unit && U ? k_move<K, ASYNC, W, false, U> : k_move<K, ASYNC, W, false, false>;
 }
 
+// The move kernel runs the stop test itself (finish_last) in launches of at most
+// this many workgroups and graphs.  Solves with a launch of its own / in the move
+// kernel, k = 8, us: planted partitions with weights, 78 workgroups (20,000
+// vertices) 334 / 327, 156 357 / 375, 312 407 / 424, 1024 (500,000) 904 / 1001;
+// grids with weights, 78 194 / 186, 176 203 / 203, 312 221 / 233, 1024 (1000^2)
+// 428 / 524; unit-weight grids, which run all their iterations, 78 245 / 225, 312
+// 311 / 290, 1024 630 / 634.  Batches of 100-vertex graphs: 128 graphs 333 / 312,
+// 256 364 / 366, 512 465 / 504 (the last workgroup tests all graphs).
+constexpr int kFuseBlocks = 128;
+constexpr int kFuseGraphs = 256;
+
 // ---------------------------------------------------------------------------
 template <int K, bool ASYNC, bool RS, bool W, bool HS = false, bool SV = false>
 static hipError_t launch_t(const Launch &launch, int grid, int merge_grid, hipStream_t s,
@@ -2422,7 +2435,10 @@ static hipError_t launch_t(const Launch &launch, int grid, int merge_grid, hipSt
   hipError_t e = hipSuccess;
   Launch L = launch;
   const bool hub_kernels = ASYNC && (L.total_hubs > 0 || L.total_merge > 0);
-  L.fuse_finish = !L.no_finish && L.total_items > 0 && !hub_kernels ? 1 : 0;
+  L.fuse_finish = !L.no_finish && L.total_items > 0 && !hub_kernels && grid <= kFuseBlocks &&
+                          L.G <= kFuseGraphs
+                      ? 1
+                      : 0;
   if (ASYNC && L.total_hubs > 0) {
     const int sg = (L.total_hubs + 255) / 256 < 1024 ? (L.total_hubs + 255) / 256 : 1024;
     hipLaunchKernelGGL(k_hub_snapshot, dim3(sg), dim3(256), 0, s, L);
