@@ -53,6 +53,30 @@ __device__ __forceinline__ Pos row_at(const RowPtr &rp, int v) {
     return as_global(rp.p32)[v];
 }
 
+// First position and length of row v, both offsets in one load: in the 64-bit
+// kernels the two widths lie in two branches, and a branch per offset put a wait
+// between the two loads of int32 offsets (a ring of 6 10^8 vertices, unit weights,
+// det, 5 iterations: 34.4 to 28.5 ms; in place 39.4 to 32.1).
+template <class Pos>
+__device__ __forceinline__ void row_of(const RowPtr &rp, int v, Pos &beg, int &len) {
+  if constexpr (sizeof(Pos) == 8) {
+    if (rp.p64) {
+      const gptr<const int64_t> p = as_global(rp.p64) + v;
+      const long long b = p[0], e = p[1];
+      beg = b;
+      len = (int)(e - b);
+    } else {
+      const gptr<const int32_t> p = as_global(rp.p32) + v;
+      const int b = p[0], e = p[1];
+      beg = (long long)(unsigned)b;
+      len = e - b;
+    }
+  } else {
+    beg = row_at<Pos>(rp, v);
+    len = (int)(row_at<Pos>(rp, v + 1) - beg);
+  }
+}
+
 // Element i of an array.  Narrow positions (Pos = int: graphs of fewer than 2^30
 // entries and vertices) are byte offsets below 2^32, which loads add to a
 // scalar base: one register per address, and none of the 64-bit sums.
@@ -1292,8 +1316,7 @@ __device__ __forceinline__ void lane_units(const MoveArgs &a, Stage<kStageT, Pos
     cv = a.C[sx];
     if (active) {
       a.act_cur[sx] = 0;
-      beg = row_at<Pos>(a.row_ptr, v);
-      len = (int)(row_at<Pos>(a.row_ptr, v + 1) - beg);
+      row_of<Pos>(a.row_ptr, v, beg, len);
     }
   }
   if (!active) len = 0;
@@ -1379,8 +1402,7 @@ __device__ __forceinline__ void short_units(const MoveArgs &a, int q0, unsigned 
     len[r] = 0;
     if (act[r]) {
       a.act_cur[sx[r]] = 0;
-      beg[r] = row_at<Pos>(a.row_ptr, v[r]);
-      len[r] = (int)(row_at<Pos>(a.row_ptr, v[r] + 1) - beg[r]);
+      row_of<Pos>(a.row_ptr, v[r], beg[r], len[r]);
     }
   }
   int c[R][D], lab[R][D];
@@ -1672,13 +1694,14 @@ using PosOf = typename std::conditional<W, long long, int>::type;
 // kernel is held to 128 registers up to k = 16, which keeps four wavefronts
 // per SIMD for the gathers (async k = 16 spills a few registers there and
 // still runs 8% faster on R-MAT-24 than with three wavefronts), and to 168
-// for k = 32 in det mode (three).  So are the det kernels of 64-bit positions
-// up to k = 8 (the 4096^2 grid with int64 offsets: 6.76 to 6.46 ms per solve;
-// R-MAT-21: 21.9 to 21.2 ms); the async ones lose by it (R-MAT-22, unit
-// weights, k = 8: 8.88 to 9.10 ms per solve) and the other instantiations are
-// left to the compiler.
+// for k = 32 in det mode (three).  So are the kernels of 64-bit positions up to k =
+// 8: det, the 4096^2 grid with int64 offsets, 6.76 to 6.46 ms per solve; async with
+// unit weights, which take 130 registers otherwise, a ring of 2^26 vertices 9.16 to
+// 7.29 ms per 10 iterations and a 3000^2 grid 1.86 to 1.71, though R-MAT-22, whose
+// long rows gain less from the fourth wavefront than the spills cost, goes from
+// 8.6 to 9.0.  The other instantiations are left to the compiler.
 template <int K, bool ASYNC, bool W>
-constexpr int kMoveWaves = W                     ? (K <= 8 && !ASYNC ? 4 : 1)
+constexpr int kMoveWaves = W                     ? (K <= 8 ? 4 : 1)
                            : (K <= 16)           ? 4
                            : (K == 32 && !ASYNC) ? 3
                                                  : 1;
