@@ -1712,9 +1712,16 @@ void k_move(Launch L) {
   move_body<K, ASYNC, false, PosOf<W>, HUBS, UNIT>(L);
 }
 
-// ... and with the double scan (LPA_RESCAN; sketch rule only).
+// ... and with the double scan (LPA_RESCAN; sketch rule only).  The det kernels are
+// held to four wavefronts where the hub chains' registers would leave three
+// (135 at k = 8), k = 8, us per solve: 1000^2 grid 1366 to 1113, with weights 859 to
+// 723, planted partitions of 10^6 vertices 2147 to 1827, R-MAT-19 12,090 to 11,950.
 template <int K, bool ASYNC, bool W>
-__global__ __launch_bounds__(kBlock) void k_move_rescan(Launch L) {
+constexpr int kRescanWaves = !ASYNC && (K <= 8 || (K == 16 && !W)) ? 4 : 1;
+
+template <int K, bool ASYNC, bool W>
+__global__ __launch_bounds__(kBlock)
+__attribute__((amdgpu_waves_per_eu(kRescanWaves<K, ASYNC, W>))) void k_move_rescan(Launch L) {
   move_body<K, ASYNC, true, PosOf<W>, !ASYNC, false>(L);
 }
 
