@@ -1285,9 +1285,11 @@ __device__ void hub_vertex_det_bm(const MoveArgs &a, int *buf, int p, unsigned l
 // n_seg].
 // ---------------------------------------------------------------------------
 // The stage keeps a step's columns for marking in the kernels whose wavefronts
-// per SIMD it leaves unchanged.
-template <int K, bool RS, class Pos, bool SV>
-constexpr bool kKeepCols = !RS && !SV && sizeof(Pos) == 4;
+// per SIMD it leaves unchanged, but not in the async one of k = 16, whose registers
+// do not hold them (31 spilled: 1000^2 grid with weights 564 to 434 us per solve, planted partitions
+// of 10^6 vertices 1139 to 1035; R-MAT-22, bound by its long rows, 8.87 to 8.90 ms).
+template <int K, bool ASYNC, bool RS, class Pos, bool SV>
+constexpr bool kKeepCols = !RS && !SV && sizeof(Pos) == 4 && !(K == 16 && ASYNC);
 
 template <int K, bool ASYNC, bool RS, class Pos, bool SV, bool UNIT>
 __device__ __forceinline__ void lane_units(const MoveArgs &a, Stage<kStageT, Pos, UNIT> &st, int u,
@@ -1322,7 +1324,7 @@ __device__ __forceinline__ void lane_units(const MoveArgs &a, Stage<kStageT, Pos
   if (!active) len = 0;
   typename SketchOf<K>::type S;
   S.clear();
-  constexpr bool KEEP = kKeepCols<K, RS, Pos, SV>;
+  constexpr bool KEEP = kKeepCols<K, ASYNC, RS, Pos, SV>;
   int kept = staged_rows<KEEP>(a, st, lane, beg, len, sx,
                                [&](int lab, float x) { S.add(lab, x); });
   scanned += (unsigned long long)len;
