@@ -522,7 +522,7 @@ struct lpa_batch {
   int total_items = 0, total_hubs = 0, total_merge = 0, total_segs = 0, unfinished = 0;
   int det_hubs = 0;   // det mode: hubs of the loaded unfinished graphs
   int max_items = 0;  // work items of the largest loaded unfinished graph
-  bool unit = false;  // no loaded unfinished graph has weights
+  bool unit = false;  // all loaded unfinished graphs: unit_stage
   bool poisoned = false;
   std::string err;
 };
@@ -553,6 +553,7 @@ struct lpa_handle {
   uint32_t *hist = nullptr;  // binning scratch
   int32_t seg_cap = 0, hub_cap = 0;
   int32_t n_segs = 0;  // hub segments planned (det mode too, for modularity)
+  bool link_cols = false;  // the kernels read the column indices over the host link
   int32_t n_mid = 0;   // lane vertices of more than kLaneExact entries (for modularity)
   double *mod_tot = nullptr;
   int mod_grid = 0;  // k_modularity workgroups (resident on every CU)
@@ -700,6 +701,14 @@ bool wide_positions(const lpa_handle *h) {
   constexpr int64_t kNarrow = (int64_t)1 << 30;
   return h->row_ptr.p64 != nullptr || h->nnz >= kNarrow || h->n >= kNarrow;
 }
+
+// Whether the unit-weight kernels run the graph: no weights, and columns in device
+// memory.  Their staging loads padding slots too, which over the host link are
+// transfers of their own.  Columns in pinned host memory, 4 iterations in place, with
+// their staging / the general one / before there were two: planted partitions of
+// 10^5 vertices 1.29 / 1.18 / 1.21 ms, R-MAT-20 42.4 / 41.3 / 41.4, 1000^2 grid
+// 2.50 / 2.43 / 2.47; only graphs of few, long rows gain (R-MAT-16 2.9 / 4.1 / 4.1).
+bool unit_stage(const lpa_handle *h) { return h->w == nullptr && !h->link_cols; }
 
 // Kernel selector: k slots, or 0 for the vote of Algorithm 3.
 int kernel_k(int k, uint32_t flags) { return (flags & LPA_RULE_BM_PAPER) ? 0 : k; }
@@ -999,7 +1008,7 @@ int batch_load(lpa_batch *b, lpa_handle *const *hs, int count) {
     const bool live = !h->finished;
     unfinished += live ? 1 : 0;
     det_hubs += live && !b->async_mode ? h->desc.n_hubs : 0;
-    unit = unit && (!live || h->w == nullptr);
+    unit = unit && (!live || unit_stage(h));
     if (live && move_items(h) > max_items) max_items = move_items(h);
     const int64_t next[4] = {
         (int64_t)pi[g] + (live ? move_items(h) : 0),
@@ -1490,7 +1499,7 @@ int stream_bin(lpa_handle *h) {
   S.grid_cap = cus * move_blocks_per_cu(kernel_k(h->k, h->flags), h->async_mode,
                                         (h->flags & LPA_RESCAN) != 0,
                                         (h->flags & LPA_SHARED_VARS) != 0,
-                                        wide_positions(h), true, h->w == nullptr);
+                                        wide_positions(h), true, unit_stage(h));
   return LPA_OK;
 }
 
@@ -1796,6 +1805,8 @@ int lpa_init(const lpa_graph *g, const float *weights, int k, double tol, int ma
     d.col = h->colr;
     d.ranked = 1;
   }
+  // a streamed graph's slices and a ranked graph's own columns are device memory
+  h->link_cols = !streamed && !d.ranked && h->nnz > 0 && pointer_location(h->col) == LPA_PTR_HOST;
   d.hub_shared = (cfg.flags & LPA_HUB_SHARED) ? 1 : 0;
   d.items = (int32_t)(h->async_mode ? lane_items((d.hub_shared ? 0 : d.n_seg) + d.n_lane, d.n_short)
                                     : d.n_hubs + lane_items(d.n_lane, d.n_short));
