@@ -506,10 +506,11 @@ struct lpa_batch {
   int32_t *d_finished = nullptr;
   uint32_t *d_ticket = nullptr;
   int32_t *d_status = nullptr;  // [3 * cap]: iter, done, dN of the last launched iteration
-  // Pinned host mirrors of the same layout, written in turn: an upload that is
+  // Two pinned host mirrors of the same layout, written in turn: an upload that is
   // still queued keeps its source while the next call prepares its own
-  // (batch_load).  The h_* pointers lie in the one written last.
-  void *hblock[2] = {nullptr, nullptr};
+  // (batch_load).  The h_* pointers lie in the one written last.  One allocation:
+  // each takes some 250 us, and every handle has a batch of its own.
+  void *hblock = nullptr;
   int mirror = 0;
   int uploads = 0;  // since the stream was last waited for
   GraphDesc *h_desc = nullptr;
@@ -913,7 +914,7 @@ int state_in(lpa_handle *h, const void *in, void *st, size_t elem, bool in_is_ho
 
 // --- batches -----------------------------------------------------------------
 void use_mirror(lpa_batch *b, int i) {
-  char *hh = (char *)b->hblock[i];
+  char *hh = (char *)b->hblock + i * b->block_bytes;
   b->mirror = i;
   b->h_desc = (GraphDesc *)hh;
   b->h_prefix = (int32_t *)(hh + b->off_prefix);
@@ -936,11 +937,10 @@ int batch_alloc(lpa_batch *b) {
     (void)hipGetLastError();
     return LPA_ERR_NOMEM;
   }
-  for (void *&hb : b->hblock)
-    if (hipHostMalloc(&hb, off, hipHostMallocDefault) != hipSuccess) {
-      (void)hipGetLastError();
-      return LPA_ERR_NOMEM;
-    }
+  if (hipHostMalloc(&b->hblock, 2 * off, hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    return LPA_ERR_NOMEM;
+  }
   char *d = (char *)b->dblock;
   b->d_desc = (GraphDesc *)d;
   b->d_prefix = (int32_t *)(d + b->off_prefix);
@@ -967,8 +967,7 @@ void batch_release(lpa_batch *b) {
   if (b->graph) (void)hipGraphDestroy(b->graph);
   if (b->cap_stream) (void)hipStreamDestroy(b->cap_stream);
   if (b->dblock) (void)hipFree(b->dblock);
-  for (void *hb : b->hblock)
-    if (hb) (void)hipHostFree(hb);
+  if (b->hblock) (void)hipHostFree(b->hblock);
   delete b;
 }
 
