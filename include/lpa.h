@@ -260,7 +260,9 @@ int lpa_init(const lpa_graph *g, const float *weights, int k, double tol,
 /* Device bytes lpa_init needs for a graph of n vertices and nnz entries
  * with these parameters (cfg NULL = defaults); the size of a caller
  * workspace (lpa_config.workspace).  The size does not depend on the
- * width of the row offsets.  LPA_ERR_ARG for nnz < 0 or nnz >= 2^62;
+ * width of the row offsets and never decreases as n or nnz grows, so that a
+ * workspace for a caller's largest graph holds the smaller ones.
+ * LPA_ERR_ARG for nnz < 0 or nnz >= 2^62;
  * LPA_ERR_UNSUPPORTED when LPA_MODE_ASYNC would split the hubs into 2^30
  * or more segments (nnz / lane_max_degree too large: raise the threshold). */
 int lpa_workspace_bytes(int32_t n, int64_t nnz, int k, int max_iter,

@@ -1090,14 +1090,17 @@ int batch_read_status(lpa_batch *b) {
 }
 
 // One launch for all iterations, a workgroup per graph (k_solve), rather than one
-// per iteration over all graphs: where each wavefront has one work item, and one
-// of them the last, ragged one of the short units too, one compute unit takes no
-// longer over an iteration than a launch and the loads behind it (unit-weight planted partitions, k = 8, us per solve with
-// a launch per iteration / in one: 200 vertices 191 / 118, 1,009 291 / 233, but
-// 2,000 297 / 343 and 4,000 309 / 527; 40 x 40 grid 219 / 135; weighted, 1,009: 344 /
-// 302; weighted, k = 16, 1,009: 472 / 450, but 1,050, 18 items: 387 / 414).  With a graph for every compute unit the two are alike, so batches of
-// more than a quarter as many keep a launch per iteration.  Per-iteration events
-// and a cap on resident workgroups need one too.
+// per iteration over all graphs: where each of its 16 wavefronts has one work item
+// and one of them a second, one compute unit takes no longer over an iteration than
+// a launch and the loads behind it.  k = 8, us per solve with a launch per iteration
+// / in one: unit-weight planted partitions of 200 vertices 229 / 102, 1,009 338 /
+// 220, weighted 379 / 280, weighted at k = 16 427 / 322; 40 x 40 grid 272 / 130;
+// 1,088 vertices with rows of 12, 17 full items, 193 / 55, weighted 247 / 184,
+// weighted at k = 16 277 / 235.  But of 2,000 vertices 297 / 343 and 4,000 309 / 527;
+// at 18 items (1,050 vertices) unit weights still gain, 279 / 248, weighted at k =
+// 16 loses, 387 / 414.  With a graph for every compute unit the two are alike, so
+// batches of more than a quarter as many keep a launch per iteration.
+// Per-iteration events and a cap on resident workgroups need one too.
 bool solve_in_one(const lpa_batch *b, const Launch &L) {
   return !b->async_mode && !b->rescan && !b->shared_vars && b->k >= 1 && b->k <= 16 && !b->wide &&
          L.det_hubs == 0 && b->blocks_cap == 0 && b->max_items <= kSolveBlock / kWave + 1 &&

@@ -1286,8 +1286,9 @@ __device__ void hub_vertex_det_bm(const MoveArgs &a, int *buf, int p, unsigned l
 // ---------------------------------------------------------------------------
 // The stage keeps a step's columns for marking in the kernels whose wavefronts
 // per SIMD it leaves unchanged, but not in the async one of k = 16, whose registers
-// do not hold them (31 spilled: 1000^2 grid with weights 564 to 434 us per solve, planted partitions
-// of 10^6 vertices 1139 to 1035; R-MAT-22, bound by its long rows, 8.87 to 8.90 ms).
+// do not hold them (31 spilled: 1000^2 grid with weights 564 to 434 us per solve,
+// planted partitions of 10^6 vertices 1139 to 1035; R-MAT-22, bound by its long
+// rows, 8.87 to 8.90 ms).
 template <int K, bool ASYNC, bool RS, class Pos, bool SV>
 constexpr bool kKeepCols = !RS && !SV && sizeof(Pos) == 4 && !(K == 16 && ASYNC);
 

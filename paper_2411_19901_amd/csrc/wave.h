@@ -23,9 +23,6 @@ __device__ __forceinline__ T rfl_as(T x) {
   else
     return rfl(x);
 }
-__device__ __forceinline__ float rfl_f(float x) {
-  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
-}
 __device__ __forceinline__ int rl(int x, int lane) { return __builtin_amdgcn_readlane(x, lane); }
 __device__ __forceinline__ float rl_f(float x, int lane) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
