@@ -1284,13 +1284,15 @@ __device__ void hub_vertex_det_bm(const MoveArgs &a, int *buf, int p, unsigned l
 // hub h = seg_hub[u] (async only); otherwise whole vertex order[n_hubs + u -
 // n_seg].
 // ---------------------------------------------------------------------------
-// The stage keeps a step's columns for marking in the kernels whose wavefronts
-// per SIMD it leaves unchanged, but not in the async one of k = 16, whose registers
-// do not hold them (31 spilled: 1000^2 grid with weights 564 to 434 us per solve,
-// planted partitions of 10^6 vertices 1139 to 1035; R-MAT-22, bound by its long
-// rows, 8.87 to 8.90 ms).
-template <int K, bool ASYNC, bool RS, class Pos, bool SV>
-constexpr bool kKeepCols = !RS && !SV && sizeof(Pos) == 4 && !(K == 16 && ASYNC);
+// The stage keeps a step's columns for marking in the kernels whose registers hold
+// them: not in the async one of k = 16 (31 spilled: 1000^2 grid with weights 564 to
+// 434 us per solve, planted partitions of 10^6 vertices 1139 to 1035; R-MAT-22, bound
+// by its long rows, 8.87 to 8.90 ms), nor in the unit-weight ones of k = 8 (9 to 19
+// spilled: 2000^2 grid in place 1045 to 998 us, planted partitions of 10^5 vertices
+// 366 to 317; 512 SBM graphs 52.8 to 52.6 ms).
+template <int K, bool ASYNC, bool RS, class Pos, bool SV, bool UNIT>
+constexpr bool kKeepCols =
+    !RS && !SV && sizeof(Pos) == 4 && !(K == 16 && ASYNC) && !(K == 8 && UNIT);
 
 template <int K, bool ASYNC, bool RS, class Pos, bool SV, bool UNIT>
 __device__ __forceinline__ void lane_units(const MoveArgs &a, Stage<kStageT, Pos, UNIT> &st, int u,
@@ -1325,7 +1327,7 @@ __device__ __forceinline__ void lane_units(const MoveArgs &a, Stage<kStageT, Pos
   if (!active) len = 0;
   typename SketchOf<K>::type S;
   S.clear();
-  constexpr bool KEEP = kKeepCols<K, ASYNC, RS, Pos, SV>;
+  constexpr bool KEEP = kKeepCols<K, ASYNC, RS, Pos, SV, UNIT>;
   int kept = staged_rows<KEEP>(a, st, lane, beg, len, sx,
                                [&](int lab, float x) { S.add(lab, x); });
   scanned += (unsigned long long)len;
@@ -1709,8 +1711,15 @@ constexpr int kMoveWaves = W                     ? (K <= 8 ? 4 : 1)
                            : (K == 32 && !ASYNC) ? 3
                                                  : 1;
 
+// No more than four for unit weights at k = 8: the det kernel would take 96
+// registers and five, which the 4096^2 grid likes (6.11 to 5.80 ms per solve), but not
+// batches of graphs (512 SBM graphs 52.6 to 54.4 ms).
+template <int K, bool W, bool UNIT>
+constexpr int kMoveMostWaves = !W && UNIT && K == 8 ? 4 : 8;
+
 template <int K, bool ASYNC, bool W, bool HUBS, bool UNIT>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kMoveWaves<K, ASYNC, W>)))
+__global__ __launch_bounds__(kBlock)
+__attribute__((amdgpu_waves_per_eu(kMoveWaves<K, ASYNC, W>, kMoveMostWaves<K, W, UNIT>)))
 void k_move(Launch L) {
   move_body<K, ASYNC, false, PosOf<W>, HUBS, UNIT>(L);
 }
