@@ -653,7 +653,8 @@ def main():
         # the single-scan kernel has instances for det launches with hubs and
         # for launches without weights
         hubs = args.mode == "det" and int((rp[1:] - rp[:-1]).max()) > lane_max
-        flags = [] if args.rescan else [hubs, w is None and kk <= 8]
+        unit = w is None and kk <= 8 and (not args.host_csr or args.ranked)
+        flags = [] if args.rescan else [hubs, unit]
         kname = (f"lpa::k_move{'_rescan' if args.rescan else ''}"
                  f"<{kk}, {'true' if args.mode == 'async' else 'false'}, {wide}"
                  + "".join(", true" if f else ", false" for f in flags) + ">")

@@ -264,15 +264,13 @@ __device__ __forceinline__ void stage_load(const MoveArgs &a, Stage<T, Pos, fals
 // UNIT: the columns of a step go into registers, all of a lane's slots in
 // flight together, the next step's while this one is consumed; then the
 // labels, eight slots at a time.  A slot past its row's end reads the row's last
-// entry (without any, another row's: staged_position) and the label of vertex
-// 0, lines that others of the step read too, so
-// no branch stands between a step's loads: it waits for memory twice, or three
-// times for 16 entries, instead of eight times in stage_load.  Such graphs have
-// no weights to stream and rows of a few labels that hit the caches, so they
-// wait more than they move: R-MAT-22 det k = 8, iterations 0 and 8, 2.7 and 2.1
-// to 1.9 and 1.3 ms; 512 SBM graphs det k = 8 55.4 to 52.9 ms per solve (at five
-// or six wavefronts per SIMD, which this stage's LDS would allow, the spills cost
-// more: 55.9 and 59.6).
+// entry (without any, another row's: staged_position) and the label of vertex 0,
+// lines that others of the step read too, so no branch stands between a step's
+// loads: it waits for memory twice, or three times for 16 entries, instead of
+// eight times in stage_load.  Such graphs have no weights to stream and rows of a
+// few labels that hit the caches, so they wait more than they move: R-MAT-22 det k =
+// 8, iterations 0 and 8, 2.7 and 2.1 to 1.9 and 1.3 ms; 512 SBM graphs det k = 8 55.4
+// to 52.6 ms per solve (at four wavefronts per SIMD: kMoveMostWaves).
 // (With weights and labels that miss, the batches of stage_load are faster: the
 // order above cost 6% on R-MAT-24, whose columns and weights then miss L2 more
 // often, 216 against 205 million line misses in the first iteration.)
@@ -1697,9 +1695,8 @@ using PosOf = typename std::conditional<W, long long, int>::type;
 
 // One iteration's label moves (single scan) ...  With 32-bit positions the
 // kernel is held to 128 registers up to k = 16, which keeps four wavefronts
-// per SIMD for the gathers (async k = 16 spills a few registers there and
-// still runs 8% faster on R-MAT-24 than with three wavefronts), and to 168
-// for k = 32 in det mode (three).  So are the kernels of 64-bit positions up to k =
+// per SIMD for the gathers (async k = 16 runs 8% faster on R-MAT-24 than with
+// three), and to 168 for k = 32 in det mode (three).  So are the kernels of 64-bit positions up to k =
 // 8: det, the 4096^2 grid with int64 offsets, 6.76 to 6.46 ms per solve; async with
 // unit weights, which take 130 registers otherwise, a ring of 2^26 vertices 9.16 to
 // 7.29 ms per 10 iterations and a 3000^2 grid 1.86 to 1.71, though R-MAT-22, whose
