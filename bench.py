@@ -644,6 +644,8 @@ def main():
     digest = source_digest()
     det_default = next((s for e, s in ((18, 64), (20, 128), (21, 256), (24, 768))
                         if g.nnz < 1 << e), 2048)
+    if args.shared_vars and g.nnz >= 1 << 24:
+        det_default = 4096
     lane_max = args.lane_max_degree or (1024 if args.mode == "async" else det_default)
     kk = args.k if args.rule == "mg" else 0  # kernel template: 0 = the vote of Algorithm 3
     wide = "true" if args.offsets64 else "false"

@@ -186,7 +186,8 @@ typedef struct lpa_config {
                               0 = default for the mode and the graph's
                               entries (async 1024; det 64 below 2^18
                               entries, 128 below 2^20, 256 below 2^21, 768
-                              below 2^24, else 2048).  Never changes
+                              below 2^24, else 2048), there 4096 with
+                              LPA_SHARED_VARS.  Never changes
                               LPA_MODE_DET results. */
   int32_t check_every;     /* lpa_run / lpa_batch_run read the convergence
                               state on the host every this many iterations

@@ -743,11 +743,14 @@ constexpr DetStep kDetSteps[] = {{(int64_t)1 << 18, 64},
                                  {(int64_t)1 << 24, 768},
                                  {INT64_MAX, 2048}};
 
-int default_lane_max(bool async_mode, int64_t nnz) {
+// shared_vars: the chain of LPA_SHARED_VARS takes some 1000 ns per entry, so large
+// graphs leave it fewer rows (R-MAT-22, unit weights, k = 8, ms per solve at S = 2048
+// / 4096: 296 / 285; R-MAT-21 158 / 158).
+int default_lane_max(bool async_mode, int64_t nnz, bool shared_vars = false) {
   if (async_mode) return 1024;
   for (const DetStep &s : kDetSteps)
-    if (nnz < s.below) return s.lane_max;
-  return kDetSteps[4].lane_max;
+    if (nnz < s.below && s.below != INT64_MAX) return s.lane_max;
+  return shared_vars ? 4096 : kDetSteps[4].lane_max;
 }
 
 // Most hubs and hub segments of a graph of nnz entries: hubs have more than S
@@ -788,7 +791,8 @@ struct Layout {
 
 size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// lane_max: the caller's threshold, 0 for the default.  bound_partials: reserve
+// lane_max: the caller's threshold, 0 for the default (LPA_SHARED_VARS then cuts
+// fewer hubs than there is room for).  bound_partials: reserve
 // the partial sketches for the largest possible number of hub segments (a caller
 // workspace); otherwise lpa_init sizes them once the segments are planned.
 Layout plan_layout(int32_t n, int64_t nnz, int k, int max_iter, bool async_mode, int lane_max,
@@ -1657,7 +1661,9 @@ int lpa_init(const lpa_graph *g, const float *weights, int k, double tol, int ma
   h->async_mode = (cfg.flags & LPA_MODE_MASK) == LPA_MODE_ASYNC;
   h->seed = seed;
   h->check_every = cfg.check_every;
-  h->lane_max = cfg.lane_max_degree > 0 ? cfg.lane_max_degree : default_lane_max(h->async_mode, h->nnz);
+  h->lane_max = cfg.lane_max_degree > 0
+                    ? cfg.lane_max_degree
+                    : default_lane_max(h->async_mode, h->nnz, (cfg.flags & LPA_SHARED_VARS) != 0);
   auto bail = [&](int code) {
     lpa_free(h);
     return code;
